@@ -40,9 +40,25 @@
 // bin's magnitude.  On the self-conjugate rows ky in {0, L/2} the slots kt and L - kt hold U
 // and conj V, and kt in {0, L/2} hold Z itself, whose real and imaginary parts are two
 // self-conjugate bins.
+//
+// The update's products.  The kernel is bound by vector issue, and a twiddle multiplication
+// per bin was its largest part.  The t loop is unrolled by four, so the row index v = 4 q + r
+// has a compile-time r, and e^{-2 pi i kt v / L} splits into quarter turns (swaps and signs)
+// and a few constants.  Cube 16, kt = 4 a + b:
+//     w^{kt v} = (-i)^{a r} * { 1, (-i)^q w^r, (-1)^q w^{2r}, (-1)^q (-i)^q w^{3r} }[b],
+// so the 16 products of one plane bin are quarter turns of four, whose real and imaginary
+// parts are x c +- y s over two multiplications for w and w^3 and one for w^2.  Cube 8,
+// kt = 2 a + b: w^{kt v} = (-i)^{a r} { 1, (-1)^q w^r }[b].  The swap of (-i)^q selects
+// between the two parts after the rounding, and its signs enter as the exact factors of the
+// fused multiply-adds into the running sums, so every sum is bit for bit that of one rounded
+// product per bin.  Per plane bin: 8 instructions (cube 16) and 2 (cube 8) beside the 2 L
+// additions, 42 and 18 with a twiddle per bin.  Whole pass, twiddle per bin -> this: 106.4 ->
+// 84.3 ms at cube 16 on 512^3 voxels, 7.33 -> 6.09 ms at cube 8 on 256 x 512 x 512, 6.9 ->
+// 5.85 ms at cube 16 and stride 4 on 512^3.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "sal_device.h"
 #include "sal_internal.h"
@@ -71,13 +87,113 @@ struct SlideGeo {
 
 __device__ __forceinline__ float mag(float re, float im) { return __builtin_amdgcn_sqrtf(fmaf(re, re, im * im)); }
 
+// (x, y) as a complex number times (-i)^K
+template <int K>
+__device__ __forceinline__ float2 quarter(float2 p)
+{
+    if constexpr ((K & 3) == 0) return p;
+    if constexpr ((K & 3) == 1) return make_float2(p.y, -p.x);
+    if constexpr ((K & 3) == 2) return make_float2(-p.x, -p.y);
+    return make_float2(-p.y, p.x);
+}
+
+// Quarter-turn state of the row v = 4 q + r: whether (-i)^q swaps the parts, the signs it
+// gives them (sx, sy), (-1)^q = s1, and the signs of (-1)^q (-i)^q (tx, ty)
+struct qturn {
+    bool odd;
+    float sx, sy, s1, tx, ty;
+};
+__device__ __forceinline__ qturn make_qturn(int q)
+{
+    const float m = -1.f, p = 1.f;
+    return {(q & 1) != 0,           (q & 2) ? m : p,       ((q + 1) & 2) ? m : p,
+            (q & 1) ? m : p,        ((q + 1) & 2) ? m : p, (q & 2) ? m : p};
+}
+
+// p w^{kt v} without the quarter turns (-i)^{a r} and the signs of take(): Q[b] of the header
+// comment with the parts already swapped
+template <int L, int R>
+__device__ __forceinline__ void products(float2 p, const qturn &t, float2 (&Q)[L == 16 ? 4 : 2])
+{
+    constexpr float C8 = 0.92387953251128674f, S8 = 0.38268343236508977f, H = 0.70710678118654752f;
+    Q[0] = p;
+    const float a = p.y * H;
+    const float2 p2 = make_float2(fmaf(p.x, H, a), fmaf(-p.x, H, a));  // p (1 - i) / sqrt 2
+    if constexpr (L == 16) {
+        auto swap = [&](float2 z) { return t.odd ? make_float2(z.y, z.x) : z; };
+        if constexpr (R == 0) {
+            Q[2] = p;
+            Q[1] = Q[3] = swap(p);
+        } else if constexpr (R == 2) {
+            Q[1] = swap(p2);
+            Q[2] = quarter<1>(p);             // w^4 = -i
+            Q[3] = swap(quarter<1>(p2));      // w^6 = -i w^2
+        } else {
+            const float yc = p.y * C8, ys = p.y * S8;
+            const float2 z1 = make_float2(fmaf(p.x, C8, ys), fmaf(-p.x, S8, yc));  // p w
+            const float2 z3 = make_float2(fmaf(p.x, S8, yc), fmaf(-p.x, C8, ys));  // p w^3
+            Q[1] = swap(R == 1 ? z1 : z3);
+            Q[2] = R == 1 ? p2 : quarter<1>(p2);
+            Q[3] = swap(R == 1 ? z3 : quarter<2>(z1));  // w^9 = -w
+        }
+    } else {
+        if constexpr (R & 1)
+            Q[1] = R == 1 ? p2 : quarter<1>(p2);  // w^3 = -i w
+        else
+            Q[1] = quarter<R / 2>(p);             // w^2 = -i
+    }
+}
+
+// (x, y) in the order of a quarter turn by K, and the signs it gives them
+template <int K>
+struct turn {
+    static constexpr bool SWAP = (K & 1) != 0;
+    static constexpr float X = (K & 2) ? -1.f : 1.f, Y = ((K + 1) & 2) ? -1.f : 1.f;
+};
+
+// D += p w^{kt v} for the slot kt = KT, from products(); the factors are +-1, so the product
+// rounded there is added exactly as it is
+template <int L, int R, int KT>
+__device__ __forceinline__ void take(float &dr, float &di, const float2 (&Q)[L == 16 ? 4 : 2], const qturn &t)
+{
+    constexpr int NB = L == 16 ? 4 : 2, A = KT / NB, B = KT % NB;
+    using T = turn<(A * R) & 3>;
+    const float2 q = Q[B];
+    float gx = 1.f, gy = 1.f;
+    if constexpr (L == 16 && B == 1) { gx = t.sx; gy = t.sy; }
+    if constexpr (L == 16 && B == 3) { gx = t.tx; gy = t.ty; }
+    if constexpr (L == 16 ? B == 2 : B == 1) gx = gy = t.s1;
+    dr = fmaf(T::X * (T::SWAP ? gy : gx), T::SWAP ? q.y : q.x, dr);
+    di = fmaf(T::Y * (T::SWAP ? gx : gy), T::SWAP ? q.x : q.y, di);
+}
+template <int L, int R, int LO, int HI>
+__device__ __forceinline__ void take_range(float *dr, float *di, const float2 (&Q)[L == 16 ? 4 : 2], const qturn &t)
+{
+    if constexpr (LO < HI) {
+        take<L, R, LO>(dr[LO], di[LO], Q, t);
+        take_range<L, R, LO + 1, HI>(dr, di, Q, t);
+    }
+}
+
+// Sums of e[0..2] over the four lane groups, (0 + 1) + (2 + 3): lane group m returns e[m]'s
+// (three lane swaps and three adds; lane group 3 repeats e[2]'s).
+__device__ __forceinline__ float group_sums(const float (&e)[3])
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(e[0]), __float_as_uint(e[1]), false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(e[2]), __float_as_uint(e[2]), false, false);
+    const float s01 = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const float s2 = __uint_as_float(c[0]) + __uint_as_float(c[1]);
+    const auto d = __builtin_amdgcn_permlane32_swap(__float_as_uint(s01), __float_as_uint(s2), false, false);
+    return __uint_as_float(d[0]) + __uint_as_float(d[1]);
+}
+
 }  // namespace
 
 template <int L, int S>
 __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2)) void k_energy_slide(
     const float *__restrict__ V, int n0, int n1, int n2, ebox bx, int nseg, int nbx, int nby,
     const float *__restrict__ w_s1, const float *__restrict__ w_s2, const float *__restrict__ w_sp,
-    const float2 *__restrict__ tw, float *__restrict__ E, float *__restrict__ vmax_part)
+    float *__restrict__ E, float *__restrict__ vmax_part)
 {
     using G = SlideGeo<L, S>;
     constexpr int SL = L, SH = G::H, SPY = G::PY, SNW = G::NW, MT = G::MT, S1S = G::S1S;
@@ -86,12 +202,11 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
     __shared__ float plane_s[2][SL * PLS];
     __shared__ float s1_s[2][SPY * S1S + 2];
     __shared__ float wt_s[SNW * 4 * SWP];
-    __shared__ float red_s[2][SNW][3][STY];
+    __shared__ float red_s[2][SNW][64];
     __shared__ float vred_s[SNW];
     // constant A operands, per lane: stage 1 [lane][K step], stage 2 [K step / 4][lane][4]
     __shared__ float4 a1_s[64];
     __shared__ float4 a2_s[MT * KS2 / 4][64];
-    __shared__ float2 tw_s[SL];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, n = lane & 15;
@@ -118,7 +233,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
     const int y_end = bx.o2 + bx.d2;
 
     for (int i = threadIdx.x; i < SNW * 4 * SWP; i += 64 * SNW) wt_s[i] = w_sp[i];
-    if (threadIdx.x < SL) tw_s[threadIdx.x] = tw[threadIdx.x];
     // (at cube 16 the 16 stage-2 operands would not fit the registers beside the 128 of the
     // spectra)
     if (threadIdx.x < 64) {
@@ -208,18 +322,16 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
 
     // E of the window completed at step jo (red_s[buf]), summed over the waves in a fixed
     // order, at the lattice windows of the box
-    auto store_energies = [&](int jo, int buf) {
+    const int ry = y_base + S * n;  // y of this lane's sums, their component is g
+    float *const E_lane = E + g * nbox + (int64_t)((x0 - bx.fo1) / S) * K2 + (ry - bx.fo2) / S;
+    const int64_t K12 = (int64_t)K1 * K2;
+    auto store_energies = [&](int jo, int buf) __attribute__((always_inline)) {
         const int t0 = s_start + jo - (SL - 1);
-        if (t0 < t_lo || (t0 - bx.o0) % S != 0 || lane >= 3 * STY) return;
-        const int m = lane >> 4, yy = lane & 15;
-        float e = red_s[buf][0][m][yy];
+        if (t0 < t_lo || (t0 - bx.o0) % S != 0) return;
+        float e = red_s[buf][0][lane];
 #pragma unroll
-        for (int w = 1; w < SNW; ++w) e += red_s[buf][w][m][yy];
-        const int y = y_base + S * yy;
-        if (y < y_end) {
-            const int64_t o = ((int64_t)((t0 - bx.fo0) / S) * K1 + (x0 - bx.fo1) / S) * K2 + (y - bx.fo2) / S;
-            E[m * nbox + o] = e;
-        }
+        for (int w = 1; w < SNW; ++w) e += red_s[buf][w][lane];
+        if (g < 3 && ry < y_end) E_lane[(t0 - bx.fo0) / S * K12] = e;
     };
 
     load_plane(0);
@@ -240,9 +352,9 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
     const float *wl = wt_s + (wave * 4 + g) * SWP;
     const bool sp_lane = g == 0;  // wave 0: lane group holding the self-conjugate rows 0, L/2
 
-#pragma unroll 1
-    for (int j = 0; j < nsteps; ++j) {
-        const int b = j & 1;
+    // step j = 4 i + R
+    auto step = [&](auto rc, int j) __attribute__((always_inline)) {
+        constexpr int R = decltype(rc)::value, b = R & 1;
         if (j + 1 < nsteps) store_plane(j + 1, b ^ 1);
         __syncthreads();
         if (j + 2 < nsteps) load_plane(j + 2);
@@ -276,61 +388,46 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
         }
 
         // ---------------- stage 3: the t update -----------------------------------------
-        const int v = (s_start - SH + j) & (SL - 1);
-        const float sh = (v & 1) ? -1.f : 1.f;  // the twiddle of kt = L/2
-        // (from LDS: a scalar load in flight would make every LDS wait of the step wait for it)
-        float2 w[SH];
-#pragma unroll
-        for (int kt = 1; kt < SH; ++kt) w[kt] = tw_s[(kt * v) & (SL - 1)];
-        // D[kt] += lo w(kt), D[L - kt] += hi conj(w(kt)), D[0] += self, D[L/2] += self sh; each
-        // product rounded before it is added
-        auto update = [&](int mt, int q, float2 lo, float2 hi, float2 self) __attribute__((always_inline)) {
-            Dr[mt][q][0] += self.x;
-            Di[mt][q][0] += self.y;
-            Dr[mt][q][SH] = fmaf(sh, self.x, Dr[mt][q][SH]);
-            Di[mt][q][SH] = fmaf(sh, self.y, Di[mt][q][SH]);
-#pragma unroll
-            for (int kt = 1; kt < SH; ++kt) {
-                const float wr = w[kt].x, wi = w[kt].y;
-                const float b1 = lo.y * wi, d1 = lo.y * wr;
-                Dr[mt][q][kt] += fmaf(lo.x, wr, -b1);
-                Di[mt][q][kt] += fmaf(lo.x, wi, d1);
-                const float b2 = hi.y * wi, d2 = hi.y * wr;
-                Dr[mt][q][SL - kt] += fmaf(hi.x, wr, b2);
-                Di[mt][q][SL - kt] += fmaf(-hi.x, wi, d2);
-            }
-        };
+        // row v = s_start - L/2 + j = 4 q + R (segment starts and L/2 are multiples of four)
+        const qturn qt = make_qturn((s_start - SH + j) >> 2);
         const int t0 = s_start + j - (SL - 1);
         const bool out = j >= SL - 1 && t0 >= t_lo && (t0 - bx.o0) % S == 0;
+        using QA = float2[SL == 16 ? 4 : 2];
         // Slot inputs.  Columns 1..L/2-1: the plane spectrum itself.  Column 0: U = P_a +
         // conj P_b and V = P_a - conj P_b for the rows (a, b = -a); on the self-conjugate rows
         // (lane group 0 of M tile 0) Z itself at kt in {0, L/2}, 2 Re Z at kt = 1..L/2-1 (U)
-        // and -2i Im Z at kt = L/2+1..L-1 (conj V).  One update code for all waves keeps the
-        // spectrum registers in place.
-        {
-            const bool w0 = wave == 0;
+        // and -2i Im Z at kt = L/2+1..L-1 (conj V).
+        float2 p[MT][2];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const float2 pa = make_float2(acc[mt][0], acc[mt][1]), pb = make_float2(acc[mt][2], acc[mt][3]);
-                const float2 u = make_float2(pa.x + pb.x, pa.y - pb.y), vv = make_float2(pa.x - pb.x, pa.y + pb.y);
-                if (mt >= 1) {
-                    const float2 p0 = w0 ? u : pa, p1 = w0 ? vv : pb;
-                    update(mt, 0, p0, p0, p0);
-                    update(mt, 1, p1, p1, p1);
-                } else if (w0) {
-                    const float2 se0 = sp_lane ? pa : u, se1 = sp_lane ? pb : vv;
-                    const float2 lo0 = sp_lane ? make_float2(2.f * pa.x, 0.f) : se0;
-                    const float2 hi0 = sp_lane ? make_float2(0.f, -2.f * pa.y) : se0;
-                    const float2 lo1 = sp_lane ? make_float2(2.f * pb.x, 0.f) : se1;
-                    const float2 hi1 = sp_lane ? make_float2(0.f, -2.f * pb.y) : se1;
-                    update(0, 0, lo0, hi0, se0);
-                    update(0, 1, lo1, hi1, se1);
-                } else {
-                    update(0, 0, pa, pa, pa);
-                    update(0, 1, pb, pb, pb);
-                }
+        for (int mt = 0; mt < MT; ++mt) {
+            const float2 pa = make_float2(acc[mt][0], acc[mt][1]), pb = make_float2(acc[mt][2], acc[mt][3]);
+            p[mt][0] = pa;
+            p[mt][1] = pb;
+            if (wave == 0 && (mt > 0 || !sp_lane)) {
+                p[mt][0] = make_float2(pa.x + pb.x, pa.y - pb.y);
+                p[mt][1] = make_float2(pa.x - pb.x, pa.y + pb.y);
             }
         }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                float *dr = Dr[mt][q], *di = Di[mt][q];
+                const float2 z = p[mt][q];
+                QA Q;
+                products<SL, R>(z, qt, Q);
+                if (mt == 0 && wave == 0) {
+                    QA Ql, Qh;
+                    products<SL, R>(sp_lane ? make_float2(2.f * z.x, 0.f) : z, qt, Ql);
+                    products<SL, R>(sp_lane ? make_float2(0.f, -2.f * z.y) : z, qt, Qh);
+                    take<SL, R, 0>(dr[0], di[0], Q, qt);
+                    take_range<SL, R, 1, SH>(dr, di, Ql, qt);
+                    take<SL, R, SH>(dr[SH], di[SH], Q, qt);
+                    take_range<SL, R, SH + 1, SL>(dr, di, Qh, qt);
+                } else {
+                    take_range<SL, R, 0, SL>(dr, di, Q, qt);
+                }
+            }
         float e[3] = {0.f, 0.f, 0.f};
         if (out && wave != 0) {
             // M tile 0: the ky of the two slots differ in lane group 0 (0 and L/2): a weight
@@ -386,16 +483,15 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
                     }
                 }
         }
-        if (out) {
-            // lanes n, n + 16, n + 32, n + 48 hold the same window
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                float s = e[m];
-                s += __shfl_xor(s, 16);
-                s += __shfl_xor(s, 32);
-                if (g == 0) red_s[b][wave][m][n] = s;
-            }
-        }
+        // lanes n, n + 16, n + 32, n + 48 hold the same window
+        if (out) red_s[b][wave][lane] = group_sums(e);
+    };
+#pragma unroll 1
+    for (int j = 0; j < nsteps; j += 4) {
+        step(std::integral_constant<int, 0>{}, j);
+        if (j + 1 < nsteps) step(std::integral_constant<int, 1>{}, j + 1);
+        if (j + 2 < nsteps) step(std::integral_constant<int, 2>{}, j + 2);
+        if (j + 3 < nsteps) step(std::integral_constant<int, 3>{}, j + 3);
     }
     __syncthreads();
     if (wave == RW) store_energies(nsteps - 1, (nsteps - 1) & 1);
@@ -441,8 +537,7 @@ static hipError_t launch_slide_L(const sal_ctx *c, const float *V, int64_t n0, i
     }
     if (nparts) *nparts = (int)nb;
     hipLaunchKernelGGL((k_energy_slide<L, S>), dim3((unsigned)nb), dim3(64 * (L / 2)), 0, s, V, (int)n0, (int)n1,
-                       (int)n2, bx, nseg, nbx, nby, c->t.w_s1, c->t.w_s2, c->t.w_sp,
-                       (const float2 *)c->t.twiddle, E, vmax_part);
+                       (int)n2, bx, nseg, nbx, nby, c->t.w_s1, c->t.w_s2, c->t.w_sp, E, vmax_part);
     return hipGetLastError();
 }
 
