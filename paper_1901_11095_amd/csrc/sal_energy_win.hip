@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "sal_device.h"
 #include "sal_dft.h"
@@ -179,6 +180,216 @@ __global__ __launch_bounds__(WinCfg<L>::NT) void k_energy_win(const float *__res
     if (tid == 0 && vmax_part) {
         float m = red_s[0][3];
         for (int v = 1; v < NWV; ++v) m = fmaxf(m, red_s[v][3]);
+        vmax_part[blockIdx.x] = m;
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// Cubes 9..15 and 17..20 with overlapping windows (stride S < L): a run of windows along y
+// shares the first two stages.  Bound by vector issue, nearly all of it the L-point DFTs:
+// k_energy_win spends 4 h L^3 + 8 h L^3 flops per window on stages A and B, which here are
+// done once per y position of the run.  The run's samples and DFTs are the windows' own, so
+// every value and every sum has the operands and the order of k_energy_win and the energies
+// are the same bit for bit, whatever run, box or crop a window is computed in.
+//   stage A  one thread per (x, y) column of the run: samples straight from global memory
+//            (rows along y are contiguous), the real DFT along t into P[mu][x][y];
+//   stage B  one thread per (mu, y): the DFT along x, in place (a thread reads and writes one
+//            column of P);
+//   stage C  lanes are the rows (mu, nu) of one window, 64 to a wave: the DFT along y of the
+//            row's L values, the magnitudes and weighted sums; then the tree of the window's
+//            rows by lane swaps and row rotations.  A wave keeps one block of 64 rows for all
+//            its windows (the weights stay in registers; om and L - om share theirs); the last
+//            block takes two or four windows at once when at most 32 or 16 rows are left, so
+//            few lanes idle.
+// The row stride of P is odd (in complex values): the lanes of stage C, one row each, hit
+// all banks.  Cube 12 on 131 x 187 x 253: 5.4 ms against 24.6 ms window by window (whole pass),
+// cube 9 to 20 on 61 x 87 x 101 between 3.5 and 6.8 times faster.
+namespace {
+
+template <int L>
+struct RunCfg {
+    static constexpr int h = L / 2 + 1, ROWS = h * L;
+    static constexpr int NB = (ROWS + 63) / 64;           // blocks of rows per window
+    static constexpr int CNT = ROWS - 64 * (NB - 1);      // rows of the last block
+    static constexpr int W = CNT <= 16 ? 16 : (CNT <= 32 ? 32 : 64);  // its lanes per window
+    static constexpr int G = 64 / W;                      // its windows per wave
+    static constexpr int NF = G > 1 ? NB - 1 : NB;        // full blocks
+    static constexpr int WB = G > 1 ? G : (NB == 1 ? 4 : 2);  // waves per full block
+    static constexpr int NWV = NF * WB + (G > 1 ? 1 : 0);
+    static constexpr int NT = 64 * NWV;
+    static constexpr int MAXRUN = 32;                     // windows of a run, at most
+};
+
+constexpr int RUN_LDS_MAX = 80 * 1024;  // P of one workgroup: at least two fit a CU
+
+__host__ __device__ constexpr int run_row_stride(int L, int S, int run) { return (S * (run - 1) + L) | 1; }
+
+// x summed over the 16 lanes of a row: rotations by 8 and 4, then quad swaps by 2 and 1 (the
+// order of the xor butterfly from 8 down to 1)
+__device__ __forceinline__ float row_sum(float x)
+{
+    auto dpp = [](float v, auto ctl) {
+        return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), decltype(ctl)::value, 0xf, 0xf, true));
+    };
+    x += dpp(x, std::integral_constant<int, 0x128>{});  // row_ror:8
+    x += dpp(x, std::integral_constant<int, 0x124>{});  // row_ror:4
+    x += dpp(x, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+    x += dpp(x, std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+    return x;
+}
+// The two outputs of a swap of a and b, added: lanes of the lower half (or even rows) hold
+// a's sum over the pair, the others b's.
+__device__ __forceinline__ float pair32(float a, float b)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float pair16(float a, float b)
+{
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+}  // namespace
+
+template <int L>
+__global__ __launch_bounds__(RunCfg<L>::NT) void k_energy_run(const float *__restrict__ V, int n0, int n1, int n2,
+                                                              ebox bx, int S, int run, WinTw<L> tw,
+                                                              const float *__restrict__ wgen, float *__restrict__ E,
+                                                              float *__restrict__ vmax_part)
+{
+    using C = RunCfg<L>;
+    constexpr int H = L / 2, h = C::h, NT = C::NT;
+    extern __shared__ float2 P[];  // [mu][x, then nu][RS]
+    __shared__ float red_s[C::NB][C::MAXRUN][3];
+    __shared__ float vred_s[C::NWV];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int box;
+    const int blk = box_tile(bx, &box);
+    V += box * bx.vstride;
+    E += box * bx.estride;
+    const int nblk = bx.table ? bx.per_box : (int)gridDim.x;
+    const int kd0 = (bx.d0 + S - 1) / S, kd1 = (bx.d1 + S - 1) / S, kd2 = (bx.d2 + S - 1) / S;
+    const int nrun = (kd2 + run - 1) / run, ntile = kd0 * kd1 * nrun;
+    const int PY = S * (run - 1) + L, RS = PY | 1;
+    const int K1 = bx.fk1, K2 = bx.fk2;
+    const int64_t nfr = (int64_t)bx.fk0 * K1 * K2;
+    const int n12 = n1 * n2;  // the volume holds at most 2^31 - 1 samples
+    float vmax = 0.f;
+
+    // stage C: this wave's block of rows, its row of each lane and the row's weights
+    const bool tail = C::G > 1 && wave == C::NF * C::WB;
+    const int rb = tail ? C::NB - 1 : wave / C::WB;
+    const int wsub = tail ? lane / C::W : 0, wstep = tail ? C::G : C::WB, wfirst = tail ? 0 : wave % C::WB;
+    const int row0 = 64 * rb + (tail ? lane % C::W : lane);
+    const bool live = row0 < C::ROWS;
+    const int row = live ? row0 : 0;
+    float wt[L / 2 + 1][3];
+#pragma unroll
+    for (int om = 0; om <= L / 2; ++om)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) wt[om][m] = wgen[(row * L + om) * 3 + m];
+
+    for (int tile = blk; tile < ntile; tile += nblk) {
+        const int kr = tile % nrun, k1 = (tile / nrun) % kd1, k0 = tile / (nrun * kd1);
+        const int p0 = bx.o0 + S * k0, p1 = bx.o1 + S * k1, p2 = bx.o2 + S * run * kr;
+        const int cnt = min(run, kd2 - run * kr);  // windows of this run
+        // ---------------- stage A: real DFT along t of every column of the run -----------
+        int rowo[L];
+#pragma unroll
+        for (int p = 0; p < L; ++p) rowo[p] = refl_idx(p0 - H + p, n0) * n12;
+        for (int c = tid; c < L * PY; c += NT) {
+            const int q = c / PY, r = c - q * PY;
+            const int off = refl_idx(p1 - H + q, n1) * n2 + refl_idx(p2 - H + r, n2);
+            float v[L];
+            float2 x[h];
+#pragma unroll
+            for (int p = 0; p < L; ++p) v[p] = V[(uint32_t)(rowo[p] + off)];
+#pragma unroll
+            for (int p = 0; p < L; ++p) vmax = fmaxf(vmax, fabsf(v[p]));
+            sal_dft::rdft_half<L>(v, tw.w, x);
+#pragma unroll
+            for (int mu = 0; mu < h; ++mu) P[(mu * L + q) * RS + r] = x[mu];
+        }
+        __syncthreads();
+        // ---------------- stage B: DFT along x per (mu, y), in place ---------------------
+        for (int c = tid; c < h * PY; c += NT) {
+            const int mu = c / PY, r = c - mu * PY;
+            float2 *col = P + mu * L * RS + r;
+            float2 a[L], f[L];
+#pragma unroll
+            for (int q = 0; q < L; ++q) a[q] = col[q * RS];
+            sal_dft::cdft<L>(a, tw.w, f);
+#pragma unroll
+            for (int nu = 0; nu < L; ++nu) col[nu * RS] = f[nu];
+        }
+        __syncthreads();
+        // ---------------- stage C: DFT along y per row (mu, nu), projections -------------
+        for (int w = wfirst; w < cnt; w += wstep) {
+            const int win = tail ? min(w + wsub, cnt - 1) : w;
+            const float2 *src = P + row * RS + S * win;
+            float2 b[L], f[L];
+#pragma unroll
+            for (int r = 0; r < L; ++r) b[r] = src[r];
+            sal_dft::cdft<L>(b, tw.w, f);
+            float e0 = 0.f, e1 = 0.f, e2 = 0.f;
+#pragma unroll
+            for (int om = 0; om < L; ++om) {
+                const int k = om <= L / 2 ? om : L - om;
+                const float m = __builtin_amdgcn_sqrtf(fmaf(f[om].x, f[om].x, f[om].y * f[om].y));
+                e0 = fmaf(wt[k][0], m, e0);
+                e1 = fmaf(wt[k][1], m, e1);
+                e2 = fmaf(wt[k][2], m, e2);
+            }
+            e0 = live ? e0 : 0.f;
+            e1 = live ? e1 : 0.f;
+            e2 = live ? e2 : 0.f;
+            // the tree of the block's 64 rows: pairs 32, 16, 8, 4, 2, 1 lanes apart (of the last
+            // block's windows, whose other rows are zero, the levels that are left)
+            if (C::G > 1 && tail) {
+                if (C::W == 32) {
+                    const float a = row_sum(pair16(e0, e1)), c = row_sum(pair16(e2, e2));
+                    // row 2 s of window s holds component 0, row 2 s + 1 component 1
+                    if ((lane & 15) == 0 && w + wsub < cnt) {
+                        red_s[rb][win][(lane >> 4) & 1] = a;
+                        if ((lane & 16) == 0) red_s[rb][win][2] = c;
+                    }
+                } else {
+                    const float a = row_sum(e0), b1 = row_sum(e1), c = row_sum(e2);
+                    if ((lane & 15) == 0 && w + wsub < cnt) {
+                        red_s[rb][win][0] = a;
+                        red_s[rb][win][1] = b1;
+                        red_s[rb][win][2] = c;
+                    }
+                }
+            } else {
+                // rows of lanes: 0 holds component 0, 2 component 1, 1 and 3 component 2
+                const float a = row_sum(pair16(pair32(e0, e1), pair32(e2, e2)));
+                if ((lane & 15) == 0 && lane < 48) red_s[rb][win][lane == 0 ? 0 : (lane == 32 ? 1 : 2)] = a;
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < 3 * run; i += NT) {
+            const int m = i / run, w = i - m * run;
+            if (w < cnt) {
+                float s = 0.f;
+#pragma unroll
+                for (int k = 0; k < C::NB; ++k) s += red_s[k][w][m];
+                const int64_t o = ((int64_t)((p0 - bx.fo0) / S) * K1 + (p1 - bx.fo1) / S) * K2 + (p2 - bx.fo2) / S + w;
+                E[m * nfr + o] = s;
+            }
+        }
+        // (the next run's stage A may write P now; red_s is rewritten two barriers later)
+    }
+    // max |V| of everything this workgroup read (all of it lies in the volume)
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o));
+    if (lane == 0) vred_s[wave] = vmax;
+    __syncthreads();
+    if (tid == 0 && vmax_part) {
+        float m = vred_s[0];
+        for (int v = 1; v < C::NWV; ++v) m = fmaxf(m, vred_s[v]);
         vmax_part[blockIdx.x] = m;
     }
 }
@@ -412,10 +623,60 @@ int64_t win_blocks(int64_t nwin, int64_t nbox)
     return nwin < WIN_BLOCKS ? (nwin > 0 ? nwin : 1) : WIN_BLOCKS;
 }
 
+// Windows per run of k_energy_run for a box of kd windows, or 0 where P would not leave room
+// for two workgroups on a CU (wide strides of the largest cubes).  At most 32, less where P is
+// too large or the runs would not give every CU two workgroups; then the runs of a row are
+// made equal (rounded up to the windows the waves take together): at cube 18 on
+// 61 x 87 x 101 rows of 3 x 32 + 5 windows took 3.27 ms, of 26 + 26 + 26 + 23 2.79 ms.
+template <int L>
+int run_length(int S, int64_t kd0, int64_t kd1, int64_t kd2, int64_t nbox)
+{
+    auto lds = [&](int run) { return RunCfg<L>::ROWS * run_row_stride(L, S, run) * (int)sizeof(float2); };
+    int run = RunCfg<L>::MAXRUN;
+    while (run > 8 && (lds(run) > RUN_LDS_MAX || kd0 * kd1 * ((kd2 + run - 1) / run) * nbox < 512)) run >>= 1;
+    if (lds(run) > RUN_LDS_MAX) return 0;
+    const int64_t nrun = (kd2 + run - 1) / run, eq = (kd2 + nrun - 1) / nrun, wb = RunCfg<L>::WB;
+    return (int)((eq + wb - 1) / wb * wb);
+}
+
+template <int L>
+hipError_t launch_run_L(const sal_ctx *c, const float *V, int64_t n0, int64_t n1, int64_t n2, ebox bx, int S, int run,
+                        float *E, float *vmax_part, int *nparts, hipStream_t s, int nbox)
+{
+    const int64_t ntile = (int64_t)((bx.d0 + S - 1) / S) * ((bx.d1 + S - 1) / S) * (((bx.d2 + S - 1) / S + run - 1) / run);
+    const size_t lds = (size_t)RunCfg<L>::ROWS * run_row_stride(L, S, run) * sizeof(float2);
+    int64_t nb;
+    if (bx.table) {
+        bx.per_box = (int)(ntile < WIN_PER_BOX ? ntile : WIN_PER_BOX);
+        nb = (int64_t)bx.per_box * nbox;
+    } else {
+        // at most WIN_BLOCKS workgroups (one partial each), in whole rounds of what 256 CUs hold
+        const int64_t fit = 256 * (160 * 1024 / (lds + 2048) < 8 ? 160 * 1024 / (lds + 2048) : 8);
+        nb = fit * (WIN_BLOCKS / fit);
+        if (ntile < nb) nb = ntile;
+    }
+    if (nparts) *nparts = (int)nb;
+    WinTw<L> tw;
+    for (int k = 0; k < L; ++k) tw.w[k] = make_float2(c->tw_host[2 * k], c->tw_host[2 * k + 1]);
+    if (lds > 65536)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_energy_run<L>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k_energy_run<L>, dim3((unsigned)nb), dim3(RunCfg<L>::NT), lds, s, V, (int)n0, (int)n1, (int)n2, bx,
+                       S, run, tw, c->t.w_gen, E, vmax_part);
+    return hipGetLastError();
+}
+
 template <int L>
 hipError_t launch_win_L(const sal_ctx *c, const float *V, int64_t n0, int64_t n1, int64_t n2, ebox bx, int S,
                         float *E, float *vmax_part, int *nparts, hipStream_t s, int nbox)
 {
+    // overlapping windows of a cube without a fused kernel share their first stages in runs
+    if constexpr (L > 8 && L != 16) {
+        const int run = S < L ? run_length<L>(S, (bx.d0 + S - 1) / S, (bx.d1 + S - 1) / S, (bx.d2 + S - 1) / S,
+                                              bx.table ? nbox : 1)
+                              : 0;
+        if (run) return launch_run_L<L>(c, V, n0, n1, n2, bx, S, run, E, vmax_part, nparts, s, nbox);
+    }
     const int64_t nwin = ((bx.d0 + S - 1) / S) * ((bx.d1 + S - 1) / S) * ((bx.d2 + S - 1) / S);
     const int64_t nb = win_blocks(nwin, bx.table ? nbox : 1);
     if (bx.table) bx.per_box = (int)(nb / nbox);
