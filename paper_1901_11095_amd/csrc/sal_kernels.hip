@@ -579,8 +579,8 @@ __global__ __launch_bounds__(256) void k_dcs_boxes(const float *__restrict__ Eb,
 }
 
 // ------------------------------------------------------------------------------------
-// Step 4, Eq. (5), tiled: a workgroup owns DTX x DTY voxels in (x, y) and walks DTT values
-// of t.  For every component m it keeps in LDS a ring of 2*ht+1 planes of E_m (ht = r if
+// Step 4, Eq. (5), tiled: a workgroup owns DTX x DTY voxels in (x, y) and walks tt <= DTT
+// values of t.  For every component m it keeps in LDS a ring of 2*ht+1 planes of E_m (ht = r if
 // m has rays along t, else 0), each plane DTX x DTY plus a halo of r along x (y) when m has
 // rays along x (y).  Planes are stored at logical coordinates with the reflection applied
 // when they are loaded, so every neighbour of Eq. (5) is a plain LDS read.  With the
@@ -590,7 +590,7 @@ constexpr int DTX = 8, DTY = 32, DTT = 32, DMAXE = 4;
 // R = r at compile time (unrolled neighbour loops), or 0 for any r.
 template <int R>
 __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, int n0, int n1,
-                                                   int n2, dcs_args a, int nbx, int nby,
+                                                   int n2, dcs_args a, int nbx, int nby, int tt,
                                                    float *__restrict__ S,
                                                    float *__restrict__ mm_part)
 {
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, 
     const int bid = blockIdx.x;
     const int ty = bid % nby, tx = (bid / nby) % nbx, tb = bid / (nby * nbx);
     const int x_base = tx * DTX, y_base = ty * DTY;
-    const int t_begin = tb * DTT, t_end = min(n0, t_begin + DTT);
+    const int t_begin = tb * tt, t_end = min(n0, t_begin + tt);
     const int tid = threadIdx.x, lx = tid / DTY, ly = tid % DTY;
     const int x = x_base + lx, y = y_base + ly;
     const bool valid = x < n1 && y < n2;
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, 
 // + ray before the - ray, s = 1..r), so all three give the same bits.
 template <int R>
 __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, int n0, int n1, int n2,
-                                                  dcs_args a, int nbx, int nby, float *__restrict__ S,
+                                                  dcs_args a, int nbx, int nby, int tt, float *__restrict__ S,
                                                   float *__restrict__ mm_part)
 {
     constexpr int D = 2 * R + 1;
@@ -780,7 +780,7 @@ __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, i
     const int bid = blockIdx.x;
     const int ty = bid % nby, tx = (bid / nby) % nbx, tb = bid / (nby * nbx);
     const int x_base = tx * DTX, y_base = ty * DTY;
-    const int t_begin = tb * DTT, t_end = min(n0, t_begin + DTT);
+    const int t_begin = tb * tt, t_end = min(n0, t_begin + tt);
     const int tid = threadIdx.x, lx = tid / DTY, ly = tid % DTY;
     const int x = x_base + lx, y = y_base + ly;
     const bool valid = x < n1 && y < n2;
@@ -1190,10 +1190,25 @@ hipError_t launch_energy_boxes(const sal_ctx *c, const float *V, int64_t n0, int
     return launch_energy_gen(c, V, n0, n1, n2, bx, E, vmax_part, nparts, s, nbox);
 }
 
+// Rows of t a workgroup of the tiled comparison walks: DTT, less while that leaves CUs
+// without a workgroup.  A walk reads 2r rows before its first output, so a short one costs
+// reads and gains nothing on a full chip; below one workgroup per CU it is latency that counts
+// (32^3 at r = 4: 23.2 us as 4 workgroups of 32 rows, 7.1 us as 32 of 4; 64^3 at r = 8: 31.3 ->
+// 9.4 us).
+static int dcs_walk(int64_t n0, int64_t n1, int64_t n2)
+{
+    const int64_t nxy = ((n1 + DTX - 1) / DTX) * ((n2 + DTY - 1) / DTY);
+    int tt = DTT;
+    while (tt > 4 && nxy * ((n0 + tt - 1) / tt) < 256) tt >>= 1;
+    return tt;
+}
+
 int64_t dcs_num_blocks(const sal_ctx *c, int64_t n0, int64_t n1, int64_t n2)
 {
-    if (dcs_tiled_lds_floats(c->p.rays, c->r) <= DCS_LDS_MAX_FLOATS)
-        return ((n1 + DTX - 1) / DTX) * ((n2 + DTY - 1) / DTY) * ((n0 + DTT - 1) / DTT);
+    if (dcs_tiled_lds_floats(c->p.rays, c->r) <= DCS_LDS_MAX_FLOATS) {
+        const int tt = dcs_walk(n0, n1, n2);
+        return ((n1 + DTX - 1) / DTX) * ((n2 + DTY - 1) / DTY) * ((n0 + tt - 1) / tt);
+    }
     const int64_t nb = (n0 * n1 * n2 + 255) / 256;
     return nb < 8192 ? nb : 8192;
 }
@@ -1212,13 +1227,13 @@ hipError_t launch_dcs(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, 
     const unsigned nb = (unsigned)dcs_num_blocks(c, n0, n1, n2);
     if (nf <= DCS_LDS_MAX_FLOATS) {
         const size_t lds = (size_t)(nf > 24 ? nf : 24) * sizeof(float);
-        const int nbx = (int)((n1 + DTX - 1) / DTX), nby = (int)((n2 + DTY - 1) / DTY);
+        const int nbx = (int)((n1 + DTX - 1) / DTX), nby = (int)((n2 + DTY - 1) / DTY), tt = dcs_walk(n0, n1, n2);
         // the default rays at a compile-time r: constant LDS offsets
         const bool axis = a.rays[0] == (SAL_RAY_PT | SAL_RAY_MT) && a.rays[1] == (SAL_RAY_PX | SAL_RAY_MX) &&
                           a.rays[2] == (SAL_RAY_PY | SAL_RAY_MY);
 #define SAL_DCS_A(RR)                                                                                            \
     case RR:                                                                                                      \
-        hipLaunchKernelGGL(k_dcs_axis<RR>, dim3(nb), dim3(256), 0, s, E, (int)n0, (int)n1, (int)n2, a, nbx, nby,  \
+        hipLaunchKernelGGL(k_dcs_axis<RR>, dim3(nb), dim3(256), 0, s, E, (int)n0, (int)n1, (int)n2, a, nbx, nby, tt, \
                            S_raw, minmax_part);                                                                   \
         return hipGetLastError();
         if (axis) {
@@ -1227,7 +1242,12 @@ hipError_t launch_dcs(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, 
                 SAL_DCS_A(2)
                 SAL_DCS_A(3)
                 SAL_DCS_A(4)
+                SAL_DCS_A(5)
+                SAL_DCS_A(6)
+                SAL_DCS_A(7)
                 SAL_DCS_A(8)
+                SAL_DCS_A(9)
+                SAL_DCS_A(10)
             default: break;
             }
         }
@@ -1237,7 +1257,7 @@ hipError_t launch_dcs(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, 
         if (lds > 65536)                                                                                          \
             (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_dcs_tiled<RR>),                           \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                      \
-        hipLaunchKernelGGL(k_dcs_tiled<RR>, dim3(nb), dim3(256), lds, s, E, (int)n0, (int)n1, (int)n2, a, nbx, nby, \
+        hipLaunchKernelGGL(k_dcs_tiled<RR>, dim3(nb), dim3(256), lds, s, E, (int)n0, (int)n1, (int)n2, a, nbx, nby, tt, \
                            S_raw, minmax_part);                                                                   \
     } while (0)
         // r known at compile time for the default d = L of every supported cube side
@@ -1246,7 +1266,12 @@ hipError_t launch_dcs(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, 
         case 2: SAL_DCS_T(2); break;
         case 3: SAL_DCS_T(3); break;
         case 4: SAL_DCS_T(4); break;
+        case 5: SAL_DCS_T(5); break;
+        case 6: SAL_DCS_T(6); break;
+        case 7: SAL_DCS_T(7); break;
         case 8: SAL_DCS_T(8); break;
+        case 9: SAL_DCS_T(9); break;
+        case 10: SAL_DCS_T(10); break;
         default: SAL_DCS_T(0); break;
         }
 #undef SAL_DCS_T
