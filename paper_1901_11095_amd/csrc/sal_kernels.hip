@@ -1097,23 +1097,30 @@ __global__ __launch_bounds__(64) void k_project(const float2 *__restrict__ F, in
 
 // ====================================================================== launchers
 
-static int tt_len_for(int64_t n0, int64_t tiles_xy)
+// Steps of the t walk.  Every step stands alone, so a walk only amortises its workgroup's
+// start (the operand tables and the first samples, some 2 us of the 56 a step takes at cube
+// 16 in split BF16), while its length is the grain of the last round of workgroups, 512 or 768
+// at a time: 32 steps where they leave at least 16 rounds, shorter down to `least` (the
+// partials of a volume are sized for two steps a workgroup; batches of boxes take none).  The
+// tile checks of 10 and 26 tiles of 32^3 in split BF16 took 3.9 ms with walks of 8 (800 and
+// 2,080 workgroups: 2 and 5 rounds), 3.4 ms with walks of 2 and 4; 128 x 256 x 256 7.82 ->
+// 7.48 ms for the pass.
+static int tt_len_for(int64_t n0, int64_t tiles_xy, int64_t least)
 {
-    // enough workgroups to fill 256 CUs several times over; long t walks otherwise
     int64_t tt = 32;
-    while (tt > 2 && tiles_xy * ((n0 + tt - 1) / tt) < 2048) tt >>= 1;
+    while (tt > least && tiles_xy * ((n0 + tt - 1) / tt) < 8192) tt >>= 1;
     return (int)tt;
 }
 
 // grid of one box (nbox > 1: the t walk is sized for that many boxes in one launch)
 template <int L>
 static void energy_grid(int64_t n0, int64_t n1, int64_t n2, int *nby, int *nbx, int *tt, int64_t *nblk,
-                        int64_t nbox = 1)
+                        int64_t nbox = 1, bool batch = false)
 {
     using C = TileCfg<L>;
     *nby = (int)((n2 + C::TY - 1) / C::TY);
     *nbx = (int)((n1 + C::NW - 1) / C::NW);
-    *tt = tt_len_for(n0, (int64_t)(*nby) * (*nbx) * nbox);
+    *tt = tt_len_for(n0, (int64_t)(*nby) * (*nbx) * nbox, batch ? 1 : 2);
     *nblk = (int64_t)(*nby) * (*nbx) * ((n0 + *tt - 1) / *tt);
 }
 
@@ -1143,7 +1150,8 @@ static hipError_t launch_energy_L(const sal_ctx *c, const float *V, int64_t n0, 
     const int S = c->p.stride;
     int nby, nbx, tt;
     int64_t nb;
-    energy_grid<L>((bx.d0 + S - 1) / S, (bx.d1 + S - 1) / S, (bx.d2 + S - 1) / S, &nby, &nbx, &tt, &nb, nbox);
+    energy_grid<L>((bx.d0 + S - 1) / S, (bx.d1 + S - 1) / S, (bx.d2 + S - 1) / S, &nby, &nbx, &tt, &nb, nbox,
+                   bx.table != nullptr);
     if (bx.table) {
         bx.per_box = (int)nb;
         nb *= nbox;
