@@ -2,12 +2,14 @@
 // layout and the launch sequence of the method (Shafiq et al., ICIP 2017, Sec. 2).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "sal_internal.h"
@@ -876,9 +878,11 @@ sal_status sal_raw_box(sal_ctx *c, const float *V, int64_t n0, int64_t n1, int64
 // E_m only along the rays of map m: with axis rays only, that is the tile grown by r along y
 // (when some ray runs along y) plus slabs of r beyond its faces along t and along x (when
 // some ray runs along them); reflected neighbours stay inside the same ranges.  With a
-// diagonal ray, the whole grown box.  Returns the boxes as {o[3], d[3]}.
+// diagonal ray, the whole grown box.  Returns the boxes as {o[3], d[3]}, the tile's own box
+// first, and for each the tile face it lies beyond: 2 axis + (0 below, 1 above), -1 for the
+// first.
 static int check_boxes(const sal_ctx *c, const int64_t lo[3], const int64_t td[3], const int64_t eo[3],
-                       const int64_t ed[3], int64_t out[5][6])
+                       const int64_t ed[3], int64_t out[5][6], int face[5])
 {
     uint32_t any = 0;
     for (int m = 0; m < 3; ++m) any |= c->p.rays[m];
@@ -888,6 +892,7 @@ static int check_boxes(const sal_ctx *c, const int64_t lo[3], const int64_t td[3
             out[k][3 + a] = d[a];
         }
     };
+    face[0] = -1;
     if (any >> 6) {
         put(0, eo, ed);
         return 1;
@@ -907,13 +912,33 @@ static int check_boxes(const sal_ctx *c, const int64_t lo[3], const int64_t td[3
         int64_t o[3] = {lo[0], lo[1], lo[2]}, d[3] = {td[0], td[1], td[2]};
         o[a] = eo[a];
         d[a] = lo[a] - eo[a];
+        face[k] = 2 * a;
         if (d[a] > 0) put(k++, o, d);
         o[a] = lo[a] + td[a];
         d[a] = eo[a] + ed[a] - o[a];
+        if (k < 5) face[k] = 2 * a + 1;
         if (d[a] > 0) put(k++, o, d);
     }
     return k;
 }
+
+// The tiles of a batch by their origin in one shared volume, to find the tile on the other
+// side of a face.
+struct TileIndex {
+    std::vector<std::pair<int64_t, int>> at;  // (linear origin, tile), sorted
+    int64_t n1, n2;
+    int64_t key(const int64_t lo[3]) const { return (lo[0] * n1 + lo[1]) * n2 + lo[2]; }
+    // the tile beyond `face` of the tile at lo, -1 if the batch has none there
+    int beyond(const int64_t lo[3], const int64_t td[3], int face) const
+    {
+        int64_t q[3] = {lo[0], lo[1], lo[2]};
+        const int a = face >> 1;
+        q[a] += (face & 1) ? td[a] : -td[a];
+        if (q[0] < 0 || q[1] < 0 || q[2] < 0 || q[1] >= n1 || q[2] >= n2) return -1;
+        const auto it = std::lower_bound(at.begin(), at.end(), std::make_pair(key(q), -1));
+        return it != at.end() && it->first == key(q) ? it->second : -1;
+    }
+};
 
 // workspace of sal_check_tiles: E of every grown box, the exact tile maps, and the tables
 // (at most five energy boxes per tile)
@@ -984,7 +1009,17 @@ sal_status sal_check_tiles(sal_ctx *c, const float *V, int64_t n0, int64_t n1, i
     if (!(bound >= 0.0)) return fail(c, SAL_E_INVAL, "bound must be >= 0");
     const int64_t n[3] = {n0, n1, n2}, m[3] = {m0, m1, m2};
     // energy boxes (ENERGY_TABLE ints each) first, then one BOX_TABLE entry per tile
-    std::vector<int> etab, ttab((size_t)nbox * BOX_TABLE, 0), ltab;
+    std::vector<int> etab, ttab((size_t)nbox * BOX_TABLE, 0), ltab, ctab;
+    // Tiles checked together lie in clusters (the edges of one body), and a slab of r beyond a
+    // face is part of the tile on the other side, whose own box computes the same energies: it
+    // is copied from there (HALO_TABLE ints per copy) instead of computed again.  An energy does
+    // not depend on the box that computes it, so the maps keep their bits.
+    TileIndex index{{}, n1, n2};
+    if (vol_stride == 0 && nbox > 1 && c->p.stride == 1) {
+        index.at.reserve((size_t)nbox);
+        for (int64_t b = 0; b < nbox; ++b) index.at.emplace_back(index.key(box_lo + 3 * b), (int)b);
+        std::sort(index.at.begin(), index.at.end());
+    }
     etab.reserve((size_t)nbox * 5 * ENERGY_TABLE);
     int64_t maxd[3] = {1, 1, 1};
     for (int64_t b = 0; b < nbox; ++b) {
@@ -1019,8 +1054,36 @@ sal_status sal_check_tiles(sal_ctx *c, const float *V, int64_t n0, int64_t n1, i
             for (int a = 0; a < 3; ++a) maxd[a] = vbox[3 + a] > maxd[a] ? vbox[3 + a] : maxd[a];
             continue;
         }
-        const int k = check_boxes(c, lo, tile_dims, eo, ed, sub);
+        int face[5], copied = 0;
+        const int k = check_boxes(c, lo, tile_dims, eo, ed, sub, face);
+        auto copy = [&](int from, const int64_t *o, const int64_t *d) {
+            const int e[HALO_TABLE] = {from, (int)b, (int)o[0], (int)o[1], (int)o[2], (int)d[0], (int)d[1], (int)d[2]};
+            ctab.insert(ctab.end(), e, e + HALO_TABLE);
+            ++copied;
+        };
+        for (int i = 1; i < k; ++i) {
+            const int a = face[i] >> 1, from = sub[i][3 + a] <= tile_dims[a] ? index.beyond(lo, tile_dims, face[i]) : -1;
+            if (from < 0) continue;
+            copy(from, sub[i], sub[i] + 3);
+            sub[i][3] = 0;  // not computed
+        }
+        // along y the tile's own box holds both halos of r; it shrinks only when both are
+        // copied (a kernel's tiles are 16 wide along y: 32 + 8 takes as many as 32 + 16), and
+        // only with two slabs copied, whose table entries make room for these
+        if (copied >= 2 && sub[0][2] == eo[2] && eo[2] == lo[2] - c->r && ed[2] == tile_dims[2] + 2 * c->r &&
+            c->r <= tile_dims[2]) {
+            const int below = index.beyond(lo, tile_dims, 4), above = index.beyond(lo, tile_dims, 5);
+            if (below >= 0 && above >= 0) {
+                const int64_t d[3] = {tile_dims[0], tile_dims[1], c->r};
+                const int64_t ob[3] = {lo[0], lo[1], lo[2] - c->r}, oa[3] = {lo[0], lo[1], lo[2] + tile_dims[2]};
+                copy(below, ob, d);
+                copy(above, oa, d);
+                sub[0][2] = lo[2];
+                sub[0][5] = tile_dims[2];
+            }
+        }
         for (int i = 0; i < k; ++i) {
+            if (sub[i][3] == 0) continue;
             const int e[ENERGY_TABLE] = {(int)sub[i][0], (int)sub[i][1], (int)sub[i][2], (int)sub[i][3],
                                          (int)sub[i][4], (int)sub[i][5], (int)eo[0], (int)eo[1], (int)eo[2],
                                          (int)ed[0], (int)ed[1], (int)ed[2], (int)b, 0, 0, 0};
@@ -1047,9 +1110,12 @@ sal_status sal_check_tiles(sal_ctx *c, const float *V, int64_t n0, int64_t n1, i
     char *ws = (char *)workspace;
     float *Eb = (float *)(ws + w.e);
     float *X = exact_out ? exact_out : (float *)(ws + w.exact);
-    int *etab_d = (int *)(ws + w.table), *ttab_d = etab_d + etab.size(), *ltab_d = ttab_d + ttab.size();
+    int *etab_d = (int *)(ws + w.table), *ttab_d = etab_d + etab.size(), *ltab_d = ttab_d + ttab.size(),
+        *ctab_d = ltab_d + ltab.size();
+    const int ncopy = (int)(ctab.size() / HALO_TABLE);
     etab.insert(etab.end(), ttab.begin(), ttab.end());
     etab.insert(etab.end(), ltab.begin(), ltab.end());
+    etab.insert(etab.end(), ctab.begin(), ctab.end());
     // stage the tables in the context's pinned buffer, once the previous upload from it is done
     if (!c->tab_done && (e = hipEventCreateWithFlags(&c->tab_done, hipEventDisableTiming)) != hipSuccess)
         return dev_fail(c, e, "event create");
@@ -1075,6 +1141,8 @@ sal_status sal_check_tiles(sal_ctx *c, const float *V, int64_t n0, int64_t n1, i
     } else {
         e = launch_energy_boxes(c, V, n0, n1, n2, vol_stride, etab_d, nent, maxd, Eb, w.estride, nullptr, nullptr, s);
         if (e != hipSuccess) return dev_fail(c, e, "energy launch");
+        e = launch_halo_copies(Eb, w.estride, ttab_d, ctab_d, ncopy, s);
+        if (e != hipSuccess) return dev_fail(c, e, "halo copy launch");
     }
     e = launch_dcs_boxes(c, Eb, w.estride, ttab_d, (int)nbox, n, tile_dims, X, s);
     if (e != hipSuccess) return dev_fail(c, e, "dcs launch");

@@ -141,6 +141,10 @@ constexpr int ENERGY_TABLE = 16;
 // predicted map
 constexpr int BOX_TABLE = 12;
 
+// ints per energy slab a tile of a batch takes from another: {from, to, o, d}, tile indices and
+// the voxels o + [0, d) of their volume
+constexpr int HALO_TABLE = 8;
+
 // A box that is its own frame.
 inline ebox framed_box(int o0, int o1, int o2, int d0, int d1, int d2, int S)
 {
@@ -199,6 +203,9 @@ hipError_t launch_energy_boxes(const sal_ctx *c, const float *V, int64_t n0, int
 // of its grown box; S_box[b][3][d0][d1][d2] written sstride floats apart
 hipError_t launch_dcs_boxes(const sal_ctx *c, const float *Eb, int64_t estride, const int *table, int nbox,
                             const int64_t n[3], const int64_t bd[3], float *S_box, hipStream_t s);
+// E of the slabs of a batch that another of its tiles holds: copied between the grown boxes'
+// frames (`tiles` the BOX_TABLE entries, `copies` ncopy HALO_TABLE entries, device)
+hipError_t launch_halo_copies(float *Eb, int64_t estride, const int *tiles, const int *copies, int ncopy, hipStream_t s);
 // error and replacement of the tiles of a batch in the predicted map (origin from the table)
 hipError_t launch_tile_merge_boxes(float *S_raw, int64_t n0, int64_t n1, int64_t n2, const float *exact,
                                    const int *table, int nbox, const int64_t td[3], const double *stats,

@@ -195,6 +195,26 @@ __global__ __launch_bounds__(256) void k_tile_copy_boxes(float *__restrict__ S, 
     }
 }
 
+// One slab of energies per group of HALO_BLOCKS workgroups: E of its voxels from the frame of
+// one tile's grown box to that of another (a slab is some 100 KB, copied within the L2).
+constexpr int HALO_BLOCKS = 8;
+__global__ __launch_bounds__(256) void k_halo_copies(float *__restrict__ Eb, int64_t estride,
+                                                     const int *__restrict__ tiles, const int *__restrict__ copies)
+{
+    const int *q = copies + HALO_TABLE * (blockIdx.x / HALO_BLOCKS);
+    const int *a = tiles + BOX_TABLE * q[0], *b = tiles + BOX_TABLE * q[1];
+    const float *src = Eb + q[0] * estride;
+    float *dst = Eb + q[1] * estride;
+    const int nv = q[5] * q[6] * q[7], na = a[3] * a[4] * a[5], nb = b[3] * b[4] * b[5];
+    for (int i = (blockIdx.x % HALO_BLOCKS) * 256 + threadIdx.x; i < nv; i += HALO_BLOCKS * 256) {
+        const int t = q[2] + i / (q[6] * q[7]), x = q[3] + (i / q[7]) % q[6], y = q[4] + i % q[7];
+        const int ia = ((t - a[0]) * a[4] + (x - a[1])) * a[5] + (y - a[2]);
+        const int ib = ((t - b[0]) * b[4] + (x - b[1])) * b[5] + (y - b[2]);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) dst[(int64_t)m * nb + ib] = src[(int64_t)m * na + ia];
+    }
+}
+
 // {min, max} of each raw map over one tile per workgroup; tiles numbered (t, x, y), y fastest.
 // A NaN in a tile makes its extremes -inf and +inf, so the check of the tiles that pass the
 // checked tiles' extremes always takes it.
@@ -315,6 +335,13 @@ hipError_t launch_tile_merge_boxes(float *S_raw, int64_t n0, int64_t n1, int64_t
                        (int)n2, exact, table, per_box, t3, stats, err);
     hipLaunchKernelGGL(k_tile_copy_boxes, dim3((unsigned)(per_box * nbox)), dim3(256), 0, s, S_raw, (int)n0,
                        (int)n1, (int)n2, exact, table, per_box, t3, err, (float)bound);
+    return hipGetLastError();
+}
+
+hipError_t launch_halo_copies(float *Eb, int64_t estride, const int *tiles, const int *copies, int ncopy, hipStream_t s)
+{
+    if (ncopy > 0)
+        hipLaunchKernelGGL(k_halo_copies, dim3((unsigned)ncopy * HALO_BLOCKS), dim3(256), 0, s, Eb, estride, tiles, copies);
     return hipGetLastError();
 }
 

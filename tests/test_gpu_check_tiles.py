@@ -202,3 +202,28 @@ def test_check_tiles_vs_oracle(L, rays):
         else:
             assert np.array_equal(P2n[(slice(None),) + sl], P.cpu().numpy()[(slice(None),) + sl])
     assert 0 < replaced < len(tiles)
+
+
+@pytest.mark.parametrize("L,prec", [(8, sal.FP32), (16, sal.FP32), (16, sal.BF16_SPLIT), (5, sal.FP32), (12, sal.FP32)])
+@pytest.mark.parametrize("td", [(16, 16, 16), (8, 12, 16), (3, 20, 9)])
+def test_clustered_tiles_share_halos(L, prec, td):
+    """Tiles that touch take the energies beyond their common faces from each other: a full
+    block of tiles reaching the volume's faces (interior tiles with neighbours on all six
+    sides), one with holes, and a lone tile, against the whole-volume maps bit for bit.  Tile
+    sides below the reach r of Eq. (5) must not share along that axis."""
+    shape = (52, 64, 60)
+    V = torch.from_numpy(synth.make_volume(shape, seed=8, n_faults=2, throw=3, n_chaotic=1, chaotic_size=12)).cuda()
+    ctx = sal.Saliency(L=L, precision=prec)
+    _, _, Sr, st = ctx.saliency_maps(V)
+    full = [(a * td[0], b * td[1], c * td[2]) for a in range(3) for b in range(3) for c in range(3)]
+    holes = [lo for j, lo in enumerate(full) if j % 4 != 1] + [tuple(n - d for n, d in zip(shape, td))]
+    for tiles in (full, holes, full[::-1], full[13:14]):
+        print("cluster L=%d td=%s of %d tiles" % (L, td, len(tiles)), flush=True)
+        P = Sr + 1.0
+        X = torch.empty((len(tiles), 3) + td, dtype=torch.float32, device="cuda")
+        err = torch.zeros(len(tiles), dtype=torch.float32, device="cuda")
+        sal.check_tiles(ctx, V, tiles, P, tiles, td, st, 0.02, err, exact_out=X)
+        for k, lo in enumerate(tiles):
+            sl = (slice(None),) + tuple(slice(a, a + d) for a, d in zip(lo, td))
+            assert torch.equal(X[k], Sr[sl]), (lo, k)
+            assert torch.equal(P[sl], Sr[sl]), (lo, k)
