@@ -124,7 +124,7 @@ __host__ __device__ inline void ray_step(int b, int &dt, int &dx, int &dy)
 // [3][fk0][fk1][fk2] with position p at index (p - fo) / S.  For one box the frame is the
 // box itself; windows still read the whole volume (reflected at its faces).
 // Batched boxes (tile checks): when `table` is set, workgroup w serves table entry
-// e = w / per_box (after the XCD-aware renumbering), whose ENERGY_TABLE ints hold
+// e = w / per_box, whose ENERGY_TABLE ints hold
 // {o, d, fo, fk, v}: the box, its frame, and the index v of its volume (which starts
 // v * vstride floats into V) and of its E (v * estride floats into E).  The grid of one
 // entry is sized for the largest box; workgroups past a smaller box exit at once.
@@ -160,11 +160,15 @@ inline ebox framed_box(int o0, int o1, int o2, int d0, int d1, int d2, int S)
 
 // Workgroup -> tile of its box; for a batch it also loads the geometry of its table entry
 // and returns in *v the index of the entry's volume and E (the caller moves its pointers).
+// One box: a contiguous range of tiles per XCD, for its L2.  A batch: in dispatch order, every
+// entry spread over all XCDs; its entries differ in size by six and more (tiles and the slabs
+// beyond their faces), and ranges of them left XCDs idle while others worked (26 tiles of 32^3
+// at cube 16 in split BF16: 1,770 us in ranges, 1,418 us so).
 __device__ __forceinline__ int box_tile(ebox &bx, int *v)
 {
-    const int t = sal_dev::xcd_tile(blockIdx.x, gridDim.x);
     *v = 0;
-    if (!bx.table) return t;
+    if (!bx.table) return sal_dev::xcd_tile(blockIdx.x, gridDim.x);
+    const int t = blockIdx.x;
     const int e = t / bx.per_box;
     const int *q = bx.table + ENERGY_TABLE * e;
     bx.o0 = q[0];
