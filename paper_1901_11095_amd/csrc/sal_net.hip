@@ -542,36 +542,77 @@ __global__ __launch_bounds__(conv_threads(CO)) void k_conv3(const void *__restri
 
 // ------------------------------------------------------------------------------------
 // Weight and bias gradient of one layer: dW[co][k][ci] = sum_v dz[v][co] in[refl(v+k-1)][ci],
-// db[co] = sum_v dz[v][co].  FP32 16x16x4 MFMA with M = co, N = ci, K = 4 voxels; wave w
-// owns taps w, w+8, w+16, w+24.  Each workgroup walks a fixed stride of tiles and writes
-// its own partial sums (summed afterwards in a fixed order: deterministic).
+// db[co] = sum_v dz[v][co].  FP32 16x16x4 MFMA with M = co, N = ci, K = 4 voxels along w.  Each
+// workgroup walks a fixed stride of tiles and writes its own partial sums (summed afterwards
+// in a fixed order: deterministic).
+//   24 input channels: wave w owns taps w, w+8, w+16, w+24; channels 16..23 of two taps share
+//     an N tile (6 MFMAs for two taps at 24 output channels instead of 8);
+//   one input channel: N = taps, waves 0..3 one (M, N) tile each.
+// Bound by the FP32 matrix work of the voxels that carry a gradient: the loss margin keeps it
+// inside the block, dz is zero on 3/4 (last layers) to 1/4 (first) of the voxels of 16^3 blocks,
+// and a K step of four zero dz adds +-0 to every sum, so it is passed over (unless the tile's
+// inputs hold an infinity or a NaN, whose product with zero counts).  The tiles stay in their
+// storage type in LDS (43 KB with BF16: the two workgroups a CU gets overlap their loads),
+// loaded 16 bytes a lane.  Batch of 64 16^3 blocks, 24 -> 24 channels: 228 us with one scalar
+// load and a division per value and every K step taken, 53, 88 and 99 us (layers 4 to 2) so.
 template <int CI, int CO, bool F32>
 __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in,
                                                      const void *__restrict__ dz_, int nb, int n0,
                                                      int n1, int n2, float *__restrict__ part)
 {
     using Act = typename ActT<F32>::type;
+    static_assert(CI == 1 || CI == 24, "taps share N tiles in the two layouts above");
+    using In = typename ActT<F32 || CI == 1>::type;  // the one-channel input is the FP32 volume
     const Act *dz = reinterpret_cast<const Act *>(dz_);
-    constexpr int MT = (CO + 15) / 16, NT = (CI + 15) / 16, NKW = 4;
-    constexpr int NPAR = CO * 27 * CI + CO;
-    __shared__ float tin[NPOS * CI];
-    __shared__ float tdz[TT * TU * TW * CO];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int MT = (CO + 15) / 16, NKW = CI == 1 ? 1 : 4, NPR = NKW / 2;
+    constexpr int NPAR = CO * 27 * CI + CO, NV = TT * TU * TW;
+    __shared__ __attribute__((aligned(16))) In tin[NPOS * CI];
+    __shared__ __attribute__((aligned(16))) Act tdz[NV * CO];
+    __shared__ uint32_t live_s[2];  // bit q: some dz of the voxels 4q .. 4q + 3 is not zero
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, n = lane & 15;
     const int ntw = (n2 + TW - 1) / TW, ntu = (n1 + TU - 1) / TU, ntt = (n0 + TT - 1) / TT;
     const int ntiles = nb * ntt * ntu * ntw;
     const int64_t vol = (int64_t)n0 * n1 * n2;
 
-    f4 acc[NKW][MT][NT];
+    auto tapoff = [](int k) { return ((k / 9) * PU + (k / 3) % 3) * PW + k % 3; };
+    // offsets of this lane's B operands from its voxel's position: channel n of the wave's taps,
+    // and channels 16..23 of two taps (lanes 0..7 the first, 8..15 the second)
+    int off[NKW], offp[NPR > 0 ? NPR : 1];
+    if constexpr (CI == 1) {
+        const int k = 16 * (wave >> 1) + n;
+        off[0] = tapoff(k < 27 ? k : 0);
+    } else {
 #pragma unroll
-    for (int a = 0; a < NKW; ++a)
+        for (int a = 0; a < NKW; ++a) off[a] = tapoff(wave + 8 * a < 27 ? wave + 8 * a : 0) * CI + n;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int q = 0; q < NPR; ++q) {
+            const int k = wave + 8 * (2 * q + (n >> 3));
+            offp[q] = tapoff(k < 27 ? k : 0) * CI + 16 + (n & 7);
+        }
+    }
+    f4 acc[NKW][MT], accp[NPR > 0 ? NPR : 1][MT];
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[a][mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+        for (int a = 0; a < NKW; ++a) acc[a][mt] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < (NPR > 0 ? NPR : 1); ++q) accp[q][mt] = f4{0.f, 0.f, 0.f, 0.f};
+    }
     float dbias = 0.f;
+    auto inf_or_nan = [](uint32_t v) {  // two BF16 values
+        return (((v & 0x7fff7fffu) + 0x00800080u) & 0x80008000u) != 0u;
+    };
 
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    // Which walk this workgroup takes: the tiles that carry a gradient recur with the blocks'
+    // period (16 tiles for 16^3), so consecutive walks go to one XCD (each then has whole
+    // blocks), shifted by half a period from one round over its CUs to the next.
+    int wg = blockIdx.x;
+    if ((gridDim.x & 511) == 0) {
+        const int i = wg >> 3, per = gridDim.x >> 3;
+        wg = (wg & 7) * per + (i & ~31) + ((i + 8 * (i >> 5)) & 31);
+    }
+    for (int tile = wg; tile < ntiles; tile += gridDim.x) {
         int bid = tile;
         const int tw_ = bid % ntw;
         bid /= ntw;
@@ -581,73 +622,175 @@ __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in
         const int b = bid / ntt;
         const int t0 = tt_ * TT, u0 = tu_ * TU, w0 = tw_ * TW;
         __syncthreads();
-        for (int i = threadIdx.x; i < NPOS * CI; i += 512) {
-            const int p = i / CI, c = i - p * CI;
+        if (threadIdx.x < 2) live_s[threadIdx.x] = 0u;
+        bool odd = false;  // an infinity or a NaN among this thread's inputs
+        auto src = [&](int p) {
             const int pt = p / (PU * PW), pu = (p / PW) % PU, pw = p % PW;
-            const int64_t gi = b * vol + ((int64_t)refl_idx(t0 - 1 + pt, n0) * n1 + refl_idx(u0 - 1 + pu, n1)) * n2 +
-                               refl_idx(w0 - 1 + pw, n2);
-            tin[i] = CI == 1 ? reinterpret_cast<const float *>(in)[gi]
-                             : from_act<F32>(reinterpret_cast<const Act *>(in)[gi * CI + c]);
+            return b * vol + ((int64_t)refl_idx(t0 - 1 + pt, n0) * n1 + refl_idx(u0 - 1 + pu, n1)) * n2 +
+                   refl_idx(w0 - 1 + pw, n2);
+        };
+        if constexpr (CI == 1) {
+            for (int p = threadIdx.x; p < NPOS; p += 512) {
+                const float v = reinterpret_cast<const float *>(in)[src(p)];
+                odd |= !(fabsf(v) < INFINITY);
+                tin[p] = v;
+            }
+        } else {
+            constexpr int CHK = CI / 8, NQ = F32 ? 2 : 1;  // chunks of 8 channels
+            for (int i = threadIdx.x; i < NPOS * CHK; i += 512) {
+                const int p = i / CHK, ch = i - p * CHK;
+                const u32x4 *q = reinterpret_cast<const u32x4 *>(reinterpret_cast<const Act *>(in) + src(p) * CI + 8 * ch);
+                u32x4 *d = reinterpret_cast<u32x4 *>(&tin[p * CI + 8 * ch]);
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) {
+                    const u32x4 v = q[k];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) odd |= F32 ? (v[e] & 0x7fffffffu) >= 0x7f800000u : inf_or_nan(v[e]);
+                    d[k] = v;
+                }
+            }
         }
-        for (int i = threadIdx.x; i < TT * TU * TW * CO; i += 512) {
-            const int vv = i / CO, c = i - vv * CO;
+        __syncthreads();  // live_s is zero
+        auto vox = [&](int vv, int64_t *gi) {
             const int gt = t0 + vv / (TU * TW), gu = u0 + (vv / TW) % TU, gw = w0 + vv % TW;
-            tdz[i] = (gt < n0 && gu < n1 && gw < n2)
-                         ? from_act<F32>(dz[(b * vol + ((int64_t)gt * n1 + gu) * n2 + gw) * CO + c])
-                         : 0.f;
+            *gi = b * vol + ((int64_t)gt * n1 + gu) * n2 + gw;
+            return gt < n0 && gu < n1 && gw < n2;
+        };
+        if constexpr (CO % 8 == 0) {
+            constexpr int CHK = CO / 8, NQ = F32 ? 2 : 1;
+            for (int i = threadIdx.x; i < NV * CHK; i += 512) {
+                const int vv = i / CHK, ch = i - vv * CHK;
+                int64_t gi;
+                u32x4 v[NQ];
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) v[k] = u32x4{0u, 0u, 0u, 0u};
+                if (vox(vv, &gi)) {
+                    const u32x4 *q = reinterpret_cast<const u32x4 *>(dz + gi * CO + 8 * ch);
+#pragma unroll
+                    for (int k = 0; k < NQ; ++k) v[k] = q[k];
+                }
+                uint32_t any = 0u;
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) {
+                    any |= v[k][0] | v[k][1] | v[k][2] | v[k][3];
+                    reinterpret_cast<u32x4 *>(&tdz[vv * CO + 8 * ch])[k] = v[k];
+                }
+                if (any & (F32 ? 0x7fffffffu : 0x7fff7fffu)) atomicOr(&live_s[vv >> 7], 1u << ((vv >> 2) & 31));
+            }
+        } else {
+            for (int i = threadIdx.x; i < NV * CO; i += 512) {
+                const int vv = i / CO, c = i - vv * CO;
+                int64_t gi;
+                const Act v = vox(vv, &gi) ? dz[gi * CO + c] : (Act)0;
+                tdz[i] = v;
+                if (from_act<F32>(v) != 0.f) atomicOr(&live_s[vv >> 7], 1u << ((vv >> 2) & 31));
+            }
         }
-        __syncthreads();
-        if (threadIdx.x < CO)
-            for (int vv = 0; vv < TT * TU * TW; ++vv) dbias += tdz[vv * CO + threadIdx.x];
-#pragma unroll 1
-        for (int v4 = 0; v4 < TT * TU * TW; v4 += 4) {
-            const int vv = v4 + g;  // this lane group's voxel
-            const int lt = vv / (TU * TW), lu = (vv / TW) % TU, lw = vv % TW;
-            float av[MT];
+        const bool all = __syncthreads_or(odd);
+        uint64_t todo = all ? ~0ull : ((uint64_t)live_s[1] << 32 | live_s[0]);
+        todo = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)todo) |
+               (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(todo >> 32)) << 32;
+        // the bias gradient: one lane per channel of the last wave, which has three taps
+        if (threadIdx.x >= 448 && threadIdx.x < 448 + CO) {
+#pragma unroll 16
+            for (int vv = 0; vv < NV; ++vv) dbias += from_act<F32>(tdz[vv * CO + threadIdx.x - 448]);
+        }
+        if (CI == 1 && (wave >= 4 || (wave & 1) >= MT)) continue;
+        // rows of 16 voxels, four K steps each: the operands' addresses are formed once per row
+        for (int row = 0; row < TT * TU; ++row) {
+            const uint32_t quads = (uint32_t)(todo >> (4 * row)) & 15u;
+            if (!quads) continue;
+            const int base = ((row / TU) * PU + row % TU) * PW + g;
+            const In *bsrc[NKW], *bpsrc[NPR > 0 ? NPR : 1];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) av[mt] = (16 * mt + n < CO) ? tdz[vv * CO + 16 * mt + n] : 0.f;
+            for (int a = 0; a < NKW; ++a) bsrc[a] = tin + base * CI + off[a];
 #pragma unroll
-            for (int a = 0; a < NKW; ++a) {
-                const int k = wave + 8 * a;
-                if (k < 27) {
-                    const int p = ((lt + k / 9) * PU + (lu + (k / 3) % 3)) * PW + lw + k % 3;
+            for (int q = 0; q < NPR; ++q) bpsrc[q] = tin + base * CI + offp[q];
+            const Act *asrc = tdz + (16 * row + g) * CO + n;
+            auto bval = [](const In *p) {
+                if constexpr (CI == 1)
+                    return *p;
+                else
+                    return from_act<F32>(*p);
+            };
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        const float bv = (16 * nt + n < CI) ? tin[p * CI + 16 * nt + n] : 0.f;
+            for (int w4 = 0; w4 < 4; ++w4) {
+                if (!(quads >> w4 & 1)) continue;
+                const int ao = 4 * w4 * CO, bo = 4 * w4 * CI;
+                if constexpr (CI == 1) {
+                    const int mt = wave & 1;
+                    const float av = 16 * mt + n < CO ? from_act<F32>(asrc[ao + 16 * mt]) : 0.f;
+                    const float bv = 16 * (wave >> 1) + n < 27 ? bval(bsrc[0] + bo) : 0.f;
+                    acc[0][0] = mfma4(av, bv, acc[0][0]);
+                } else {
+                    float av[MT];
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt)
-                            acc[a][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[mt], bv, acc[a][mt][nt], 0, 0, 0);
+                    for (int mt = 0; mt < MT; ++mt)
+                        av[mt] = (16 * mt + n < CO) ? from_act<F32>(asrc[ao + 16 * mt]) : 0.f;
+#pragma unroll
+                    for (int q = 0; q < NPR; ++q) {
+                        const float b0 = bval(bsrc[2 * q] + bo), bp = bval(bpsrc[q] + bo);
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) acc[2 * q][mt] = mfma4(av[mt], b0, acc[2 * q][mt]);
+                        if (wave + 8 * (2 * q + 1) < 27) {
+                            const float b1 = bval(bsrc[2 * q + 1] + bo);
+#pragma unroll
+                            for (int mt = 0; mt < MT; ++mt) acc[2 * q + 1][mt] = mfma4(av[mt], b1, acc[2 * q + 1][mt]);
+                        }
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) accp[q][mt] = mfma4(av[mt], bp, accp[q][mt]);
                     }
                 }
             }
         }
     }
-    float *pp = part + (int64_t)blockIdx.x * NPAR;
+    float *pp = part + (int64_t)wg * NPAR;
+    if (threadIdx.x >= 448 && threadIdx.x < 448 + CO) pp[CO * 27 * CI + threadIdx.x - 448] = dbias;
+    if constexpr (CI == 1) {
+        const int k = 16 * (wave >> 1) + n;
+        if (wave < 4 && (wave & 1) < MT && k < 27)
 #pragma unroll
-    for (int a = 0; a < NKW; ++a) {
-        const int k = wave + 8 * a;
-        if (k >= 27) continue;
+            for (int j = 0; j < 4; ++j) {
+                const int co = 16 * (wave & 1) + 4 * g + j;
+                if (co < CO) pp[co * 27 + k] = acc[0][0][j];
+            }
+    } else {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
+            for (int j = 0; j < 4; ++j) {
+                const int co = 16 * mt + 4 * g + j;
+                if (co >= CO) continue;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int co = 16 * mt + 4 * g + j, ci = 16 * nt + n;
-                    if (co < CO && ci < CI) pp[(co * 27 + k) * CI + ci] = acc[a][mt][nt][j];
+                for (int a = 0; a < NKW; ++a)
+                    if (wave + 8 * a < 27) pp[(co * 27 + wave + 8 * a) * CI + n] = acc[a][mt][j];
+#pragma unroll
+                for (int q = 0; q < NPR; ++q) {
+                    const int k = wave + 8 * (2 * q + (n >> 3));
+                    if (k < 27) pp[(co * 27 + k) * CI + 16 + (n & 7)] = accp[q][mt][j];
                 }
+            }
     }
-    if (threadIdx.x < CO) pp[CO * 27 * CI + threadIdx.x] = dbias;
 }
 
-// grad[j] += sum over partials (fixed order)
-__global__ __launch_bounds__(256) void k_sum_partials(const float *__restrict__ part, int nparts,
-                                                      int npar, float *__restrict__ grad)
+// grad[j] += sum over partials (fixed order: one after the other, with 16 loads in flight).  A
+// step reads 32 MB of partials for a 24 -> 24 layer, through 244 waves (61 workgroups of four
+// and one load at a time took 122 us, 14 us so).
+__global__ __launch_bounds__(64) void k_sum_partials(const float *__restrict__ part, int nparts,
+                                                     int npar, float *__restrict__ grad)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x;
+    const int j = blockIdx.x * 64 + threadIdx.x;
     if (j >= npar) return;
     float s = 0.f;
-    for (int p = 0; p < nparts; ++p) s += part[(int64_t)p * npar + j];
+    int p = 0;
+    for (; p + 16 <= nparts; p += 16) {
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = part[(int64_t)(p + i) * npar + j];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s += v[i];
+    }
+    for (; p < nparts; ++p) s += part[(int64_t)p * npar + j];
     grad[j] += s;
 }
 
@@ -913,7 +1056,7 @@ void wgrad(sal_net *n, int l, const void *in, const void *dz, int64_t nb, int64_
     hipLaunchKernelGGL((k_conv3_wgrad<CI, CO, F32>), dim3(grid), dim3(512), 0, s, in, dz, (int)nb, (int)n0,
                        (int)n1, (int)n2, part);
     const int npar = CO * 27 * CI + CO;
-    hipLaunchKernelGGL(k_sum_partials, dim3((npar + 255) / 256), dim3(256), 0, s, part, grid, npar,
+    hipLaunchKernelGGL(k_sum_partials, dim3((npar + 63) / 64), dim3(64), 0, s, part, grid, npar,
                        n->gr + n->woff[l]);
 }
 

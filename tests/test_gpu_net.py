@@ -334,3 +334,45 @@ def test_params_roundtrip_and_output_scale(net):
             assert torch.equal(Y2[c], Y1[c] * s), c
     finally:
         net.set_output_scale(old)
+
+
+@pytest.mark.parametrize("voxels", [((5, 5, 5),), ((7, 6, 15), (10, 12, 5)), ((15, 15, 15),)])
+def test_f32_gradient_of_few_voxels(net32, voxels):
+    """A gradient on one or two voxels: almost every K step of the weight gradients holds only
+    zeros and is passed over, the ones around the voxels are not (same bound and reference as
+    the dense case; 21 is no multiple of the 4 x 4 x 16 tile)."""
+    S = 21
+    X, dY = _grad_case(S, 77)
+    keep = np.zeros((S, S, S, 1), bool)
+    for v in voxels:
+        keep[v] = True
+    dY = (dY * keep).astype(np.float32)
+    Xg = torch.from_numpy(X).cuda()
+    net32.grads(zero=True)
+    net32.forward(Xg)
+    net32.backward(Xg, torch.from_numpy(dY).cuda())
+    g = net32.grads(zero=True).astype(np.float64)
+    ref = O.net_backward(X[..., None], net32.get_params().astype(np.float64), dY)
+    for l, sw, sb in _layers(g):
+        ew, eb = relmax(g[sw], ref[sw]), relmax(g[sb], ref[sb])
+        assert ew <= 1e-5 and eb <= 1e-5, (l, ew, eb)
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+@pytest.mark.parametrize("prec", [sal.FP32, sal.BF16])
+def test_nonfinite_input_reaches_the_gradient(bad, prec):
+    """An infinity or a NaN among the inputs of voxels whose gradient is zero: zero times it is
+    NaN, which no passed-over K step may hide."""
+    net = sal.Net(seed=5)
+    net.set_precision(prec)
+    S = 13
+    X, dY = _grad_case(S, 3)
+    X[0, 0, 0, 0] = bad
+    Xg = torch.from_numpy(X).cuda()
+    net.forward(Xg)
+    net.backward(Xg, torch.from_numpy(dY).cuda())
+    g = net.grads(zero=True)
+    sw = next(_layers(g))[1]
+    w = g[sw].reshape(24, 27)
+    # tap 0 of the corner voxel's neighbours reads it, also for output voxels without gradient
+    assert np.isnan(w).any()
