@@ -860,13 +860,13 @@ sal_status sal_raw_box(sal_ctx *c, const float *V, int64_t n0, int64_t n1, int64
         // the lattice energies around the grown box, interpolated onto it
         float *El = (float *)(ws + off);
         off += align256((size_t)3 * kd[0] * kd[1] * kd[2] * sizeof(float));
-        e = launch_energy(c, V, n0, n1, n2, vbox, El, (float *)(ws + off), nullptr, s);
+        e = launch_energy(c, V, n0, n1, n2, vbox, El, nullptr, nullptr, s);
         if (e != hipSuccess) return dev_fail(c, e, "energy launch");
         e = launch_upsample_box(El, kd, klo, K, c->p.stride, eo, ed, Eb, s);
         if (e != hipSuccess) return dev_fail(c, e, "upsample launch");
     } else {
         const int64_t box[6] = {eo[0], eo[1], eo[2], ed[0], ed[1], ed[2]};
-        e = launch_energy(c, V, n0, n1, n2, box, Eb, (float *)(ws + off), nullptr, s);
+        e = launch_energy(c, V, n0, n1, n2, box, Eb, nullptr, nullptr, s);
         if (e != hipSuccess) return dev_fail(c, e, "energy launch");
     }
     e = launch_dcs_box(c, Eb, eo, ed, n, box_lo, box_dims, S_raw_box, s);

@@ -191,7 +191,7 @@ __device__ __forceinline__ float group_sums(const float (&e)[3])
 
 template <int L, int S>
 __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2)) void k_energy_slide(
-    const float *__restrict__ V, int n0, int n1, int n2, ebox bx, int nseg, int nbx, int nby,
+    const float *__restrict__ V, int n0, int n1, int n2, ebox bx, int nseg, int np, int nbx, int nby,
     const float *__restrict__ w_s1, const float *__restrict__ w_s2, const float *__restrict__ w_sp,
     float *__restrict__ E, float *__restrict__ vmax_part)
 {
@@ -223,23 +223,29 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
     const int ncol = nbx * nby;
     if (bx.table) {
         const int tile = box_tile(bx, &box);
-        kr = (tile / nbx) % nseg;
-        col = tile / (nbx * nseg) * nbx + tile % nbx;
+        kr = (tile / nbx) % (nseg * np);
+        col = tile / (nbx * nseg * np) * nbx + tile % nbx;
     } else {
         const int per = (ncol + 7) >> 3, i = blockIdx.x >> 3;
         kr = i / per;
         col = (blockIdx.x & 7) * per + (i - kr * per);
         if (col >= ncol) return;
-        kr = kr + 1 < nseg ? kr + 1 : 0;
+        kr = kr + np < nseg * np ? kr + np : kr + np - nseg * np;
     }
+    // part kp of the np parts of the segment's windows: the later ones repeat the updates of the
+    // earlier ones without their magnitudes
+    const int kp = kr % np;
+    kr /= np;
     V += box * bx.vstride;
     E += box * bx.estride;
     const int xr = col % nbx, ty = col / nbx;
     const int y_base = bx.o2 + S * STY * ty, x0 = bx.o1 + S * xr;
     const int k = slide_seg_id(bx.o0, SH) + kr;
     const int s_start = slide_seg_start(k, SH);
-    const int t_lo = max(s_start, bx.o0), t_hi = min(slide_seg_start(k + 1, SH), min(n0, bx.o0 + bx.d0));
-    float *const vmax_out = vmax_part ? vmax_part + kr * ncol + col : nullptr;
+    const int w_lo = max(s_start, bx.o0), w_hi = min(slide_seg_start(k + 1, SH), min(n0, bx.o0 + bx.d0));
+    const int w_per = ((w_hi - w_lo + np - 1) / np + S - 1) / S * S;
+    const int t_lo = w_lo + kp * w_per, t_hi = min(w_hi, t_lo + w_per);
+    float *const vmax_out = vmax_part ? vmax_part + (kr * np + kp) * ncol + col : nullptr;
     if (kr >= nseg || t_lo >= t_hi || x0 >= bx.o1 + bx.d1 || y_base >= bx.o2 + bx.d2) {
         if (threadIdx.x == 0 && vmax_out) *vmax_out = 0.f;
         return;
@@ -529,10 +535,26 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
 // touched by the box rows [o0, o0 + d0); the grid covers the most any box of the batch needs.
 static int slide_nseg(int o0, int d0, int r) { return slide_seg_id(o0 + d0 - 1, r) - slide_seg_id(o0, r) + 1; }
 
+// Parts a segment's windows are split into: one, more while the chip would not get two
+// workgroups per CU at cube 8 (one at cube 16: eight waves of 256 registers) and a part keeps
+// eight windows.  Each part repeats the earlier ones' updates, without magnitudes (a third of
+// a step's vector work, 0.7 of its time when one workgroup has a CU to itself), so splitting
+// only pays in latency, on idle CUs: 32^3 at cube 8 31.4 us in one part, 27.1 in two, 25.6 in
+// four; at cube 16 85 -> 73; 128 x 24 x 30 at cube 16 320 -> 244.  The sums are the same chain
+// of additions, bit for bit.
+static int slide_parts(int L, int64_t nseg, int64_t ncol, int64_t d0)
+{
+    const int64_t slots = L == 8 ? 512 : 256;
+    int np = 1;
+    while (np < 8 && 2 * np * nseg * ncol <= slots && d0 >= 16 * np) np *= 2;
+    return np;
+}
+
 int64_t energy_slide_num_blocks(const sal_ctx *c, int64_t n0, int64_t n1, int64_t n2)
 {
     const int64_t S = c->p.stride, k1 = (n1 + S - 1) / S, k2 = (n2 + S - 1) / S;
-    return (int64_t)slide_nseg(0, (int)n0, c->L / 2) * k1 * ((k2 + STY - 1) / STY);
+    const int64_t nseg = slide_nseg(0, (int)n0, c->L / 2), ncol = k1 * ((k2 + STY - 1) / STY);
+    return nseg * slide_parts(c->L, nseg, ncol, n0) * ncol;
 }
 
 template <int L, int S>
@@ -546,16 +568,17 @@ static hipError_t launch_slide_L(const sal_ctx *c, const float *V, int64_t n0, i
         nseg = slide_nseg(bx.o0, bx.d0, L / 2);
     // lattice windows of the box along x, groups of 16 along y
     const int nbx = (bx.d1 + S - 1) / S, nby = ((bx.d2 + S - 1) / S + STY - 1) / STY;
-    int64_t nb = (int64_t)nseg * nbx * nby;
+    const int np = slide_parts(L, nseg, (int64_t)nbx * nby * (bx.table ? nbox : 1), bx.d0);
+    int64_t nb = (int64_t)nseg * np * nbx * nby;
     if (nparts) *nparts = (int)nb;  // (a batch takes no partials)
     if (bx.table) {
         bx.per_box = (int)nb;
         nb *= nbox;
     } else {
-        nb = 8 * (((int64_t)nbx * nby + 7) / 8) * nseg;  // eight equal column ranges
+        nb = 8 * (((int64_t)nbx * nby + 7) / 8) * nseg * np;  // eight equal column ranges
     }
     hipLaunchKernelGGL((k_energy_slide<L, S>), dim3((unsigned)nb), dim3(64 * (L / 2)), 0, s, V, (int)n0, (int)n1,
-                       (int)n2, bx, nseg, nbx, nby, c->t.w_s1, c->t.w_s2, c->t.w_sp, E, vmax_part);
+                       (int)n2, bx, nseg, np, nbx, nby, c->t.w_s1, c->t.w_s2, c->t.w_sp, E, vmax_part);
     return hipGetLastError();
 }
 

@@ -150,3 +150,22 @@ def test_slide_strided_boxes_equal_whole_volume(maps2, lo, dims):
     box = ctx.raw_box(Vd, lo, dims).cpu().numpy()
     sl = (slice(None),) + tuple(slice(a, a + d) for a, d in zip(lo, dims))
     assert np.array_equal(box, Sr[sl])
+
+
+@pytest.mark.parametrize("L,stride", [(8, 1), (8, 3), (16, 1), (16, 5)])
+@pytest.mark.parametrize("rows", [39, 128])
+def test_small_volumes_in_parts(L, stride, rows):
+    """Few columns: a segment's windows are split over workgroups that repeat the earlier
+    updates (up to eight parts, the last ones short or empty).  Against the oracle, and bit for
+    bit equal to the same rows of boxes that take other parts of the walk."""
+    V = synth.make_volume((rows, 11, 18), seed=rows + L, n_faults=1, throw=3)
+    ctx = sal.Saliency(L=L, stride=stride)
+    Vd = torch.from_numpy(V).cuda()
+    S, E, Sr, st = ctx.saliency_maps(Vd)
+    ref = O.saliency(V, O.Params(L=L, stride=stride))
+    for m in range(3):
+        assert relmax(E[m].cpu().numpy(), ref["E"][m]) <= 1e-5, m
+    assert float(st[6]) == float(np.abs(V).max())
+    for lo, d in ((0, 3), (L // 2 - 1, 5), (17, 12), (rows - 7, 7)):
+        box = ctx.raw_box(Vd, (lo, 1, 2), (d, 9, 15))
+        assert torch.equal(box, Sr[:, lo:lo + d, 1:10, 2:17]), lo
