@@ -619,22 +619,37 @@ __global__ __launch_bounds__(256) void k_dcs_boxes(const float *__restrict__ Eb,
 // default rays each E value is read from memory about 1.4 times instead of 2r+1 times.
 constexpr int DTX = 8, DTY = 32, DTT = 32, DMAXE = 4;
 
+// Output box and E frame of the tiled comparison: the voxels bo + [0, bd) of the volume, written
+// box-local, from E given on the positions eo + [0, ed) (the whole volume, or a box that holds
+// every reflected neighbour of the output box).
+struct dcs_frame {
+    int eo0, eo1, eo2, ed0, ed1, ed2, bo0, bo1, bo2, bd0, bd1, bd2;
+};
+// Index in a frame's axis (origin o, size d) of volume position u, reflected in [0, n); clamped
+// for the padding positions of edge tiles, whose results are never stored.
+__device__ __forceinline__ int frame_idx(int u, int n, int o, int d)
+{
+    const int i = refl_idx(u, n) - o;
+    return i < 0 ? 0 : (i >= d ? d - 1 : i);
+}
+
 // R = r at compile time (unrolled neighbour loops), or 0 for any r.
 template <int R>
 __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, int n0, int n1,
-                                                   int n2, dcs_args a, int nbx, int nby, int tt,
+                                                   int n2, dcs_frame fr, dcs_args a, int nbx, int nby, int tt,
                                                    float *__restrict__ S,
                                                    float *__restrict__ mm_part)
 {
     extern __shared__ float lds[];
-    const int64_t plane = (int64_t)n1 * n2, N = plane * n0;
+    const int64_t plane = (int64_t)fr.ed1 * fr.ed2, N = plane * fr.ed0;
+    const int64_t NS = (int64_t)fr.bd0 * fr.bd1 * fr.bd2;
     const int bid = blockIdx.x;
     const int ty = bid % nby, tx = (bid / nby) % nbx, tb = bid / (nby * nbx);
     const int x_base = tx * DTX, y_base = ty * DTY;
-    const int t_begin = tb * tt, t_end = min(n0, t_begin + tt);
+    const int t_begin = tb * tt, t_end = min(fr.bd0, t_begin + tt);
     const int tid = threadIdx.x, lx = tid / DTY, ly = tid % DTY;
     const int x = x_base + lx, y = y_base + ly;
-    const bool valid = x < n1 && y < n2;
+    const bool valid = x < fr.bd1 && y < fr.bd2;
     const int r = R > 0 ? R : a.r;
     float g[R > 0 ? R : 32];
 #pragma unroll
@@ -662,11 +677,13 @@ __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, 
         for (int e = 0; e < DMAXE; ++e) {
             const int i = tid + 256 * e;
             const int ix = i / W[m], iy = i - ix * W[m];
-            gofs[m][e] = i < HW[m] ? refl_idx(x_base - hx[m] + ix, n1) * n2 + refl_idx(y_base - hy[m] + iy, n2) : -1;
+            gofs[m][e] = i < HW[m] ? frame_idx(fr.bo1 + x_base - hx[m] + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
+                                         frame_idx(fr.bo2 + y_base - hy[m] + iy, n2, fr.eo2, fr.ed2)
+                                   : -1;
         }
     float pv[3][DMAXE];
     auto fetch = [&](int m, int tl) {
-        const float *src = E + m * N + (int64_t)refl_idx(tl, n0) * plane;
+        const float *src = E + m * N + (int64_t)frame_idx(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane;
 #pragma unroll
         for (int e = 0; e < DMAXE; ++e) pv[m][e] = gofs[m][e] >= 0 ? src[gofs[m][e]] : 0.f;
     };
@@ -697,7 +714,7 @@ __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, 
         }
         __syncthreads();
         if (valid) {
-            const int64_t ov = ((int64_t)t * n1 + x) * n2 + y;
+            const int64_t ov = ((int64_t)t * fr.bd1 + x) * fr.bd2 + y;
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
                 const uint32_t rm = a.rays[m];
@@ -759,7 +776,7 @@ __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, 
                     }
                 }
                 const float sv = a.Q[m] > 0.f ? sum / a.Q[m] : 0.f;
-                S[m * N + ov] = sv;
+                S[m * NS + ov] = sv;
                 mn[m] = fminf(mn[m], sv);
                 mx[m] = fmaxf(mx[m], sv);
             }
@@ -797,7 +814,8 @@ __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, 
 // + ray before the - ray, s = 1..r), so all three give the same bits.
 template <int R>
 __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, int n0, int n1, int n2,
-                                                  dcs_args a, int nbx, int nby, int tt, float *__restrict__ S,
+                                                  dcs_frame fr, dcs_args a, int nbx, int nby, int tt,
+                                                  float *__restrict__ S,
                                                   float *__restrict__ mm_part)
 {
     constexpr int D = 2 * R + 1;
@@ -808,14 +826,15 @@ __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, i
     __shared__ float pl2[HW2];
     __shared__ float red[4 * 6];
 
-    const int64_t plane = (int64_t)n1 * n2, N = plane * n0;
+    const int64_t plane = (int64_t)fr.ed1 * fr.ed2, N = plane * fr.ed0;
+    const int64_t NS = (int64_t)fr.bd0 * fr.bd1 * fr.bd2;
     const int bid = blockIdx.x;
     const int ty = bid % nby, tx = (bid / nby) % nbx, tb = bid / (nby * nbx);
     const int x_base = tx * DTX, y_base = ty * DTY;
-    const int t_begin = tb * tt, t_end = min(n0, t_begin + tt);
+    const int t_begin = tb * tt, t_end = min(fr.bd0, t_begin + tt);
     const int tid = threadIdx.x, lx = tid / DTY, ly = tid % DTY;
     const int x = x_base + lx, y = y_base + ly;
-    const bool valid = x < n1 && y < n2;
+    const bool valid = x < fr.bd1 && y < fr.bd2;
     float g[R];
 #pragma unroll
     for (int s = 0; s < R; ++s) g[s] = a.g[s];
@@ -825,18 +844,22 @@ __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, i
 #pragma unroll
     for (int e = 0; e < N1; ++e) {
         const int i = tid + 256 * e, ix = i / W1, iy = i % W1;
-        o1[e] = i < HW1 ? refl_idx(x_base - R + ix, n1) * n2 + refl_idx(y_base + iy, n2) : -1;
+        o1[e] = i < HW1 ? frame_idx(fr.bo1 + x_base - R + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
+                              frame_idx(fr.bo2 + y_base + iy, n2, fr.eo2, fr.ed2)
+                        : -1;
     }
 #pragma unroll
     for (int e = 0; e < N2; ++e) {
         const int i = tid + 256 * e, ix = i / W2, iy = i % W2;
-        o2[e] = i < HW2 ? refl_idx(x_base + ix, n1) * n2 + refl_idx(y_base - R + iy, n2) : -1;
+        o2[e] = i < HW2 ? frame_idx(fr.bo1 + x_base + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
+                              frame_idx(fr.bo2 + y_base - R + iy, n2, fr.eo2, fr.ed2)
+                        : -1;
     }
-    const int o0 = valid ? x * n2 + y : 0;
+    const int o0 = valid ? (fr.bo1 + x - fr.eo1) * fr.ed2 + (fr.bo2 + y - fr.eo2) : 0;
     float col[D], nxt = 0.f, p1[N1], p2[N2];
-    auto at0 = [&](int tl) { return E[(int64_t)refl_idx(tl, n0) * plane + o0]; };
+    auto at0 = [&](int tl) { return E[(int64_t)frame_idx(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane + o0]; };
     auto fetch12 = [&](int tl) {
-        const float *src1 = E + N + (int64_t)refl_idx(tl, n0) * plane, *src2 = src1 + N;
+        const float *src1 = E + N + (int64_t)frame_idx(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane, *src2 = src1 + N;
 #pragma unroll
         for (int e = 0; e < N1; ++e) p1[e] = o1[e] >= 0 ? src1[o1[e]] : 0.f;
 #pragma unroll
@@ -863,7 +886,7 @@ __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, i
         }
         __syncthreads();
         if (valid) {
-            const int64_t ov = ((int64_t)t * n1 + x) * n2 + y;
+            const int64_t ov = ((int64_t)t * fr.bd1 + x) * fr.bd2 + y;
             float sum[3];
             {   // map t: plane t + d in col[R + d]
                 const float c = col[R];
@@ -897,7 +920,7 @@ __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, i
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
                 const float sv = a.Q[m] > 0.f ? sum[m] / a.Q[m] : 0.f;
-                S[m * N + ov] = sv;
+                S[m * NS + ov] = sv;
                 mn[m] = fminf(mn[m], sv);
                 mx[m] = fmaxf(mx[m], sv);
             }
@@ -1255,8 +1278,7 @@ int64_t dcs_num_blocks(const sal_ctx *c, int64_t n0, int64_t n1, int64_t n2)
     return nb < 8192 ? nb : 8192;
 }
 
-hipError_t launch_dcs(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, int64_t n2,
-                      float *S_raw, float *minmax_part, hipStream_t s)
+static dcs_args dcs_args_of(const sal_ctx *c)
 {
     dcs_args a;
     a.r = c->r;
@@ -1265,62 +1287,77 @@ hipError_t launch_dcs(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, 
         a.Q[m] = c->Q[m];
     }
     for (int i = 0; i < 96; ++i) a.g[i] = c->g[i];
+    return a;
+}
+
+// The tiled comparison on a frame (its rays' planes fit the LDS).
+static hipError_t launch_dcs_frame(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, int64_t n2,
+                                   const dcs_frame &fr, float *S_raw, float *minmax_part, hipStream_t s)
+{
+    const dcs_args a = dcs_args_of(c);
     const int64_t nf = dcs_tiled_lds_floats(c->p.rays, c->r);
-    const unsigned nb = (unsigned)dcs_num_blocks(c, n0, n1, n2);
-    if (nf <= DCS_LDS_MAX_FLOATS) {
-        const size_t lds = (size_t)(nf > 24 ? nf : 24) * sizeof(float);
-        const int nbx = (int)((n1 + DTX - 1) / DTX), nby = (int)((n2 + DTY - 1) / DTY), tt = dcs_walk(n0, n1, n2);
-        // the default rays at a compile-time r: constant LDS offsets
-        const bool axis = a.rays[0] == (SAL_RAY_PT | SAL_RAY_MT) && a.rays[1] == (SAL_RAY_PX | SAL_RAY_MX) &&
-                          a.rays[2] == (SAL_RAY_PY | SAL_RAY_MY);
-#define SAL_DCS_A(RR)                                                                                            \
-    case RR:                                                                                                      \
-        hipLaunchKernelGGL(k_dcs_axis<RR>, dim3(nb), dim3(256), 0, s, E, (int)n0, (int)n1, (int)n2, a, nbx, nby, tt, \
-                           S_raw, minmax_part);                                                                   \
+    const unsigned nb = (unsigned)dcs_num_blocks(c, fr.bd0, fr.bd1, fr.bd2);
+    const size_t lds = (size_t)(nf > 24 ? nf : 24) * sizeof(float);
+    const int nbx = (fr.bd1 + DTX - 1) / DTX, nby = (fr.bd2 + DTY - 1) / DTY,
+              tt = dcs_walk(fr.bd0, fr.bd1, fr.bd2);
+    // the default rays at a compile-time r: constant LDS offsets
+    const bool axis = a.rays[0] == (SAL_RAY_PT | SAL_RAY_MT) && a.rays[1] == (SAL_RAY_PX | SAL_RAY_MX) &&
+                      a.rays[2] == (SAL_RAY_PY | SAL_RAY_MY);
+#define SAL_DCS_A(RR)                                                                                               \
+    case RR:                                                                                                         \
+        hipLaunchKernelGGL(k_dcs_axis<RR>, dim3(nb), dim3(256), 0, s, E, (int)n0, (int)n1, (int)n2, fr, a, nbx, nby, tt, \
+                           S_raw, minmax_part);                                                                      \
         return hipGetLastError();
-        if (axis) {
-            switch (c->r) {
-                SAL_DCS_A(1)
-                SAL_DCS_A(2)
-                SAL_DCS_A(3)
-                SAL_DCS_A(4)
-                SAL_DCS_A(5)
-                SAL_DCS_A(6)
-                SAL_DCS_A(7)
-                SAL_DCS_A(8)
-                SAL_DCS_A(9)
-                SAL_DCS_A(10)
-            default: break;
-            }
-        }
-#undef SAL_DCS_A
-#define SAL_DCS_T(RR)                                                                                            \
-    do {                                                                                                          \
-        if (lds > 65536)                                                                                          \
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_dcs_tiled<RR>),                           \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                      \
-        hipLaunchKernelGGL(k_dcs_tiled<RR>, dim3(nb), dim3(256), lds, s, E, (int)n0, (int)n1, (int)n2, a, nbx, nby, tt, \
-                           S_raw, minmax_part);                                                                   \
-    } while (0)
-        // r known at compile time for the default d = L of every supported cube side
+    if (axis) {
         switch (c->r) {
-        case 1: SAL_DCS_T(1); break;
-        case 2: SAL_DCS_T(2); break;
-        case 3: SAL_DCS_T(3); break;
-        case 4: SAL_DCS_T(4); break;
-        case 5: SAL_DCS_T(5); break;
-        case 6: SAL_DCS_T(6); break;
-        case 7: SAL_DCS_T(7); break;
-        case 8: SAL_DCS_T(8); break;
-        case 9: SAL_DCS_T(9); break;
-        case 10: SAL_DCS_T(10); break;
-        default: SAL_DCS_T(0); break;
+            SAL_DCS_A(1)
+            SAL_DCS_A(2)
+            SAL_DCS_A(3)
+            SAL_DCS_A(4)
+            SAL_DCS_A(5)
+            SAL_DCS_A(6)
+            SAL_DCS_A(7)
+            SAL_DCS_A(8)
+            SAL_DCS_A(9)
+            SAL_DCS_A(10)
+        default: break;
         }
-#undef SAL_DCS_T
-    } else {
-        hipLaunchKernelGGL(k_dcs, dim3(nb), dim3(256), 0, s, E, (int)n0, (int)n1, (int)n2, a,
-                           S_raw, minmax_part);
     }
+#undef SAL_DCS_A
+#define SAL_DCS_T(RR)                                                                                               \
+    do {                                                                                                             \
+        if (lds > 65536)                                                                                             \
+            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_dcs_tiled<RR>),                              \
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                         \
+        hipLaunchKernelGGL(k_dcs_tiled<RR>, dim3(nb), dim3(256), lds, s, E, (int)n0, (int)n1, (int)n2, fr, a, nbx, nby, \
+                           tt, S_raw, minmax_part);                                                                  \
+    } while (0)
+    // r known at compile time for the default d = L of every supported cube side
+    switch (c->r) {
+    case 1: SAL_DCS_T(1); break;
+    case 2: SAL_DCS_T(2); break;
+    case 3: SAL_DCS_T(3); break;
+    case 4: SAL_DCS_T(4); break;
+    case 5: SAL_DCS_T(5); break;
+    case 6: SAL_DCS_T(6); break;
+    case 7: SAL_DCS_T(7); break;
+    case 8: SAL_DCS_T(8); break;
+    case 9: SAL_DCS_T(9); break;
+    case 10: SAL_DCS_T(10); break;
+    default: SAL_DCS_T(0); break;
+    }
+#undef SAL_DCS_T
+    return hipGetLastError();
+}
+
+hipError_t launch_dcs(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, int64_t n2,
+                      float *S_raw, float *minmax_part, hipStream_t s)
+{
+    const int d0 = (int)n0, d1 = (int)n1, d2 = (int)n2;
+    if (dcs_tiled_lds_floats(c->p.rays, c->r) <= DCS_LDS_MAX_FLOATS)
+        return launch_dcs_frame(c, E, n0, n1, n2, dcs_frame{0, 0, 0, d0, d1, d2, 0, 0, 0, d0, d1, d2}, S_raw, minmax_part, s);
+    hipLaunchKernelGGL(k_dcs, dim3((unsigned)dcs_num_blocks(c, n0, n1, n2)), dim3(256), 0, s, E, d0, d1, d2,
+                       dcs_args_of(c), S_raw, minmax_part);
     return hipGetLastError();
 }
 
@@ -1414,13 +1451,15 @@ hipError_t launch_dcs_box(const sal_ctx *c, const float *Eb, const int64_t eo[3]
                           const int64_t n[3], const int64_t bo[3], const int64_t bd[3], float *S,
                           hipStream_t s)
 {
-    dcs_args a;
-    a.r = c->r;
-    for (int m = 0; m < 3; ++m) {
-        a.rays[m] = c->p.rays[m];
-        a.Q[m] = c->Q[m];
+    // the tiled kernels read each E about 1.4 times instead of once per ray and step; the sums run
+    // in one order in all of them (box of 64 x 256 x 320 at r = 8: 304 us with k_dcs_box, 43 us tiled)
+    if (dcs_tiled_lds_floats(c->p.rays, c->r) <= DCS_LDS_MAX_FLOATS) {
+        auto i = [](const int64_t *v, int k) { return (int)v[k]; };
+        const dcs_frame fr{i(eo, 0), i(eo, 1), i(eo, 2), i(ed, 0), i(ed, 1), i(ed, 2),
+                           i(bo, 0), i(bo, 1), i(bo, 2), i(bd, 0), i(bd, 1), i(bd, 2)};
+        return launch_dcs_frame(c, Eb, n[0], n[1], n[2], fr, S, nullptr, s);
     }
-    for (int i = 0; i < 96; ++i) a.g[i] = c->g[i];
+    const dcs_args a = dcs_args_of(c);
     const int64_t nb = bd[0] * bd[1] * bd[2];
     const unsigned blocks = (unsigned)((nb + 255) / 256 < 4096 ? (nb + 255) / 256 : 4096);
     auto i3 = [](const int64_t *v) { return make_int3((int)v[0], (int)v[1], (int)v[2]); };
@@ -1432,13 +1471,7 @@ hipError_t launch_dcs_box(const sal_ctx *c, const float *Eb, const int64_t eo[3]
 hipError_t launch_dcs_boxes(const sal_ctx *c, const float *Eb, int64_t estride, const int *table, int nbox,
                             const int64_t n[3], const int64_t bd[3], float *S_box, hipStream_t s)
 {
-    dcs_args a;
-    a.r = c->r;
-    for (int m = 0; m < 3; ++m) {
-        a.rays[m] = c->p.rays[m];
-        a.Q[m] = c->Q[m];
-    }
-    for (int i = 0; i < 96; ++i) a.g[i] = c->g[i];
+    const dcs_args a = dcs_args_of(c);
     const int64_t nb = bd[0] * bd[1] * bd[2];
     const int per_box = (int)((nb + 255) / 256 < 64 ? (nb + 255) / 256 : 64);
     hipLaunchKernelGGL(k_dcs_boxes, dim3((unsigned)(per_box * nbox)), dim3(256), 0, s, Eb, estride, table,
