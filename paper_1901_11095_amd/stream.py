@@ -38,12 +38,14 @@ def _slabs(n0: int, slab: int, halo: int, align: int = 1):
 def raw_maps_streamed(V_host: torch.Tensor, compute, halo: int, slab: int = 64,
                       S_raw: Optional[torch.Tensor] = None, device="cuda",
                       keep: Optional[torch.Tensor] = None, ctx: Optional[sal.Saliency] = None,
-                      align: int = 1):
+                      align: int = 1, part=None):
     """Raw maps [3, n0, n1, n2] (device) of a pinned host volume; `compute(Vslab)` returns
     the raw maps [3, m, n1, n2] of a device slab [m, n1, n2].  With `keep` (device
     [n0, n1, n2]) the rows of every slab are also kept there as they pass.  max|V| is
     reduced slab by slab by the library (sal_absmax on `ctx`, or a plain FP32 context).
-    Returns (S_raw, max|V|)."""
+    `part(Vslab, lo, hi)`, when given, is called instead of `compute` and returns the maps of
+    the slab's rows [lo, hi) only, so nothing is computed for the halo but what those rows
+    read.  Returns (S_raw, max|V|)."""
     n0, n1, n2 = V_host.shape
     dev = torch.device(device)
     if S_raw is None:
@@ -80,8 +82,10 @@ def raw_maps_streamed(V_host: torch.Tensor, compute, halo: int, slab: int = 64,
             upload(i + 1)
         comp.wait_event(ready[k])
         Vs = bufs[k][:b - a]
-        out = compute(Vs)
-        S_raw[:, s0:s1].copy_(out[:, s0 - a:s1 - a])
+        if part is not None:
+            S_raw[:, s0:s1].copy_(part(Vs, s0 - a, s1 - a))
+        else:
+            S_raw[:, s0:s1].copy_(compute(Vs)[:, s0 - a:s1 - a])
         if keep is not None:
             keep[s0:s1].copy_(Vs[s0 - a:s1 - a])
         sal.absmax(red, Vs[s0 - a:s1 - a], vmax, accumulate=i > 0)
@@ -96,12 +100,17 @@ def plain_streamed(ctx: sal.Saliency, V_host: torch.Tensor, slab: int = 64):
     st = ctx.params.stride
     halo = ctx.L // 2 + ctx.params.d // 2 + (st if st > 1 else 0)
 
-    def compute(Vs):
-        o = torch.empty((3,) + tuple(Vs.shape), dtype=torch.float32, device=Vs.device)
-        ctx.saliency(Vs, S_raw_out=o)
-        return o
+    # The raw maps of the slab's own rows: energies on those and r = d/2 more, no Eq. (6) per slab.
+    # A whole slab computes 2 halo more rows of all of it: 192 x 256 x 320, cube 16, slabs of 64
+    # 16.2 ms, the rows alone 13.8 ms.
+    n1, n2 = V_host.shape[1:]
+    ws = torch.empty(ctx.raw_box_workspace_size((min(slab, V_host.shape[0]), n1, n2)), dtype=torch.uint8,
+                     device="cuda")
 
-    S_raw, vmax = raw_maps_streamed(V_host, compute, halo, slab, ctx=ctx, align=st)
+    def part(Vs, lo, hi):
+        return ctx.raw_box(Vs, (lo, 0, 0), (hi - lo, n1, n2), workspace=ws)
+
+    S_raw, vmax = raw_maps_streamed(V_host, None, halo, slab, ctx=ctx, align=st, part=part)
     stats = torch.zeros(8, dtype=torch.float64, device=S_raw.device)
     S = sal.normalize_combine(ctx, S_raw, None, stats_out=stats, vmax=vmax)
     return S, S_raw, stats

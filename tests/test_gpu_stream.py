@@ -100,3 +100,30 @@ def test_surrogate_streamed_tiles_within_bound(net):
     assert torch.equal(res["S_raw"], ref["S_raw"])
     assert torch.equal(res["S"], ref["S"])
     assert bool(torch.isfinite(res["S"]).all())
+
+
+@pytest.mark.parametrize("L,shape,slab,kw", [
+    (16, (150, 40, 36), 24, {}),               # windows sliding along t, slabs below the halo
+    (16, (90, 33, 36), 100, {}),               # one slab
+    (8, (100, 20, 33), 17, {}),                # ragged last slab
+    (5, (50, 20, 21), 16, {}),
+    (12, (60, 24, 26), 25, {}),
+    (16, (80, 32, 40), 30, {"stride": 4}),     # slabs off the lattice rows
+])
+def test_plain_streamed_rows_equal_whole_slabs(L, shape, slab, kw):
+    """Raw maps of a slab's own rows against those of the whole slab, row by row the same
+    sums: bit for bit."""
+    V = synth.make_volume(shape, seed=5, n_faults=1, throw=3, n_chaotic=1, chaotic_size=8)
+    ctx = sal.Saliency(L=L, **kw)
+    st = ctx.params.stride
+
+    def whole(Vs):
+        o = torch.empty((3,) + tuple(Vs.shape), dtype=torch.float32, device=Vs.device)
+        ctx.saliency(Vs, S_raw_out=o)
+        return o
+
+    halo = L // 2 + ctx.params.d // 2 + (st if st > 1 else 0)
+    ref, _ = stream.raw_maps_streamed(stream.pinned(V), whole, halo, slab, ctx=ctx, align=st)
+    _, Sr, _ = stream.plain_streamed(ctx, stream.pinned(V), slab=slab)
+    torch.cuda.synchronize()
+    assert torch.equal(Sr, ref)
