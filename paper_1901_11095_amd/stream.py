@@ -100,17 +100,23 @@ def plain_streamed(ctx: sal.Saliency, V_host: torch.Tensor, slab: int = 64):
     st = ctx.params.stride
     halo = ctx.L // 2 + ctx.params.d // 2 + (st if st > 1 else 0)
 
+    def compute(Vs):
+        o = torch.empty((3,) + tuple(Vs.shape), dtype=torch.float32, device=Vs.device)
+        ctx.saliency(Vs, S_raw_out=o)
+        return o
+
     # The raw maps of the slab's own rows: energies on those and r = d/2 more, no Eq. (6) per slab.
     # A whole slab computes 2 halo more rows of all of it: 192 x 256 x 320, cube 16, slabs of 64
-    # 16.2 ms, the rows alone 13.8 ms.
-    n1, n2 = V_host.shape[1:]
-    ws = torch.empty(ctx.raw_box_workspace_size((min(slab, V_host.shape[0]), n1, n2)), dtype=torch.uint8,
-                     device="cuda")
+    # 16.2 ms, the rows alone 13.8 ms.  A box has at most 2^20 voxels along an axis, a volume more.
+    part = None
+    box = (min(slab, V_host.shape[0]),) + tuple(V_host.shape[1:])
+    if max(box) <= 1 << 20:
+        ws = torch.empty(ctx.raw_box_workspace_size(box), dtype=torch.uint8, device="cuda")
 
-    def part(Vs, lo, hi):
-        return ctx.raw_box(Vs, (lo, 0, 0), (hi - lo, n1, n2), workspace=ws)
+        def part(Vs, lo, hi):
+            return ctx.raw_box(Vs, (lo, 0, 0), (hi - lo,) + box[1:], workspace=ws)
 
-    S_raw, vmax = raw_maps_streamed(V_host, None, halo, slab, ctx=ctx, align=st, part=part)
+    S_raw, vmax = raw_maps_streamed(V_host, compute, halo, slab, ctx=ctx, align=st, part=part)
     stats = torch.zeros(8, dtype=torch.float64, device=S_raw.device)
     S = sal.normalize_combine(ctx, S_raw, None, stats_out=stats, vmax=vmax)
     return S, S_raw, stats
