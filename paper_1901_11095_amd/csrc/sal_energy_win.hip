@@ -195,47 +195,82 @@ __global__ __launch_bounds__(WinCfg<L>::NT) void k_energy_win(const float *__res
 //            (rows along y are contiguous), the real DFT along t into P[mu][x][y];
 //   stage B  one thread per (mu, y): the DFT along x, in place (a thread reads and writes one
 //            column of P);
-//   stage C  lanes are the rows (mu, nu) of one window, 64 to a wave: the DFT along y of the
-//            row's L values, the magnitudes and weighted sums; then the tree of the window's
-//            rows by lane swaps and row rotations.  A wave keeps one block of 64 rows for all
-//            its windows (the weights stay in registers; om and L - om share theirs); the last
-//            block takes two or four windows at once when at most 32 or 16 rows are left, so
-//            few lanes idle.
+//   stage C  one thread per row (mu, nu) of a window, as many windows at once as the threads
+//            hold (the weights stay in registers; om and L - om share theirs): the DFT along y
+//            of the row's L values, the magnitudes and weighted sums; then the tree of the
+//            window's rows.  Where a window's rows fill whole waves the tree is lane swaps and
+//            row rotations and no wave waits for another.  Elsewhere threads take rows across
+//            waves, without gaps, and one wave at a time sums the tree from LDS.  Of the rows nu
+//            and L - nu of a real t spectrum (mu = 0 and L/2), conjugates bin for bin, one
+//            thread then transforms one and sums both, its magnitudes in either order.
 // The row stride of P is odd (in complex values): the lanes of stage C, one row each, hit
-// all banks.  Cube 12 on 131 x 187 x 253: 5.4 ms against 24.6 ms window by window (whole pass),
-// cube 9 to 20 on 61 x 87 x 101 between 3.5 and 6.8 times faster.
+// all banks.  Cube 12 on 131 x 187 x 253: 4.45 ms against 24.6 ms window by window (whole pass);
+// with 64 rows of one window to a wave at every side, 96 lanes for its 84 rows, 5.4 ms.  Energies
+// of 96 x 100 x 120, 64 rows to a wave -> this: cube 9 460 -> 387 us, 11 1,059 -> 743, 13 1,303 ->
+// 1,069, 14 1,413 -> 1,251, 17 3,934 -> 2,696, 18 4,968 -> 2,967, 19 5,424 -> 4,207 and 20 6,480 ->
+// 5,034 (the last two as whole waves in sets of four).
 namespace {
 
 template <int L>
 struct RunCfg {
     static constexpr int h = L / 2 + 1, ROWS = h * L;
-    static constexpr int NB = (ROWS + 63) / 64;           // blocks of rows per window
-    static constexpr int CNT = ROWS - 64 * (NB - 1);      // rows of the last block
-    static constexpr int W = CNT <= 16 ? 16 : (CNT <= 32 ? 32 : 64);  // its lanes per window
-    static constexpr int G = 64 / W;                      // its windows per wave
-    static constexpr int NF = G > 1 ? NB - 1 : NB;        // full blocks
-    static constexpr int WB = G > 1 ? G : (NB == 1 ? 4 : 2);  // waves per full block
-    static constexpr int NWV = NF * WB + (G > 1 ? 1 : 0);
-    static constexpr int NT = 64 * NWV;
-    static constexpr int MAXRUN = 32;                     // windows of a run, at most
+    static constexpr int NB = (ROWS + 63) / 64;  // blocks of rows in the sum's tree
+    static constexpr int REAL = 2 - L % 2;       // mu with a real t spectrum: 0 (and L/2)
+    static constexpr int M = (L - 1) / 2;        // conjugate rows (nu, L - nu) of each
+    // Waves: whole sets of four, one per SIMD.  (With 3, 5, 6 or 7 the barriers wait for the
+    // fullest SIMD: cube 12 5.2 to 6.4 ms with fewer idle lanes than four's 4.5 ms.)  More than
+    // four meet more of the others at every barrier, so they have to need a fifth fewer lanes per
+    // window (cube 10 546 us with four, 897 with twelve that need a seventh fewer).
+    static constexpr int waves()
+    {
+        int best = 4, lanes = 64 * 4 / (64 * 4 / (ROWS - REAL * M));
+        for (int n = 8; n <= 12; n += 4) {
+            const int l = 64 * n / (64 * n / (ROWS - REAL * M));
+            if (5 * l < 4 * lanes) {
+                best = n;
+                lanes = l;
+            }
+        }
+        return best;
+    }
+    static constexpr int NWV = waves(), NT = 64 * NWV;
+    // a window's rows in waves of their own where that takes no more waves
+    static constexpr bool OWN = NT / (64 * NB) >= NT / (ROWS - REAL * M);
+    static constexpr int PAIR = OWN ? 0 : REAL * M;  // conjugate pairs, a thread for both rows
+    static constexpr int R = OWN ? 64 * NB : ROWS - PAIR;  // threads per window
+    static constexpr int G = NT / R;             // windows transformed together
+    static constexpr int ES = 64 * NB + 4;       // floats per window and component
+    static constexpr int MAXRUN = 32;            // windows of a run, up to a multiple of G
+    // floats of e_s: [run's window][component][block], or two of [window of G][component][row]
+    static constexpr int NE = OWN ? MAXRUN * 3 * NB : 2 * G * 3 * ES;
+    // registers for two workgroups of eight waves on a CU
+    static constexpr int OCC = NWV == 8 ? 4 : 1;
+    static_assert(G >= 1 && (!OWN || MAXRUN % G == 0), "threads for a window, e_s for a run");
 };
 
 constexpr int RUN_LDS_MAX = 80 * 1024;  // P of one workgroup: at least two fit a CU
 
 __host__ __device__ constexpr int run_row_stride(int L, int S, int run) { return (S * (run - 1) + L) | 1; }
 
-// x summed over the 16 lanes of a row: rotations by 8 and 4, then quad swaps by 2 and 1 (the
-// order of the xor butterfly from 8 down to 1)
+template <int CTL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTL, 0xf, 0xf, true));
+}
+// x summed over the four lanes of a quad: pairs 2, then 1 lane apart
+__device__ __forceinline__ float quad_sum(float x)
+{
+    x += dpp<0x4E>(x);  // quad_perm [2,3,0,1]
+    x += dpp<0xB1>(x);  // quad_perm [1,0,3,2]
+    return x;
+}
+// x summed over the 16 lanes of a row: rotations by 8 and 4, then the quad (the order of the xor
+// butterfly from 8 down to 1)
 __device__ __forceinline__ float row_sum(float x)
 {
-    auto dpp = [](float v, auto ctl) {
-        return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), decltype(ctl)::value, 0xf, 0xf, true));
-    };
-    x += dpp(x, std::integral_constant<int, 0x128>{});  // row_ror:8
-    x += dpp(x, std::integral_constant<int, 0x124>{});  // row_ror:4
-    x += dpp(x, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
-    x += dpp(x, std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
-    return x;
+    x += dpp<0x128>(x);  // row_ror:8
+    x += dpp<0x124>(x);  // row_ror:4
+    return quad_sum(x);
 }
 // The two outputs of a swap of a and b, added: lanes of the lower half (or even rows) hold
 // a's sum over the pair, the others b's.
@@ -253,7 +288,7 @@ __device__ __forceinline__ float pair16(float a, float b)
 }  // namespace
 
 template <int L>
-__global__ __launch_bounds__(RunCfg<L>::NT) void k_energy_run(const float *__restrict__ V, int n0, int n1, int n2,
+__global__ __launch_bounds__(RunCfg<L>::NT, RunCfg<L>::OCC) void k_energy_run(const float *__restrict__ V, int n0, int n1, int n2,
                                                               ebox bx, int S, int run, WinTw<L> tw,
                                                               const float *__restrict__ wgen, float *__restrict__ E,
                                                               float *__restrict__ vmax_part)
@@ -261,7 +296,7 @@ __global__ __launch_bounds__(RunCfg<L>::NT) void k_energy_run(const float *__res
     using C = RunCfg<L>;
     constexpr int H = L / 2, h = C::h, NT = C::NT;
     extern __shared__ float2 P[];  // [mu][x, then nu][RS]
-    __shared__ float red_s[C::NB][C::MAXRUN][3];
+    __shared__ float e_s[C::NE];
     __shared__ float vred_s[C::NWV];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -278,18 +313,52 @@ __global__ __launch_bounds__(RunCfg<L>::NT) void k_energy_run(const float *__res
     const int n12 = n1 * n2;  // the volume holds at most 2^31 - 1 samples
     float vmax = 0.f;
 
-    // stage C: this wave's block of rows, its row of each lane and the row's weights
-    const bool tail = C::G > 1 && wave == C::NF * C::WB;
-    const int rb = tail ? C::NB - 1 : wave / C::WB;
-    const int wsub = tail ? lane / C::W : 0, wstep = tail ? C::G : C::WB, wfirst = tail ? 0 : wave % C::WB;
-    const int row0 = 64 * rb + (tail ? lane % C::W : lane);
-    const bool live = row0 < C::ROWS;
-    const int row = live ? row0 : 0;
+    // stage C: this thread's window of the G and its row; conjugate pairs in the first threads
+    constexpr int NPR = C::G * C::PAIR, SINGLE = C::R - C::PAIR, SELF = C::REAL * C::REAL;
+    const bool pair = tid < NPR;
+    bool live = tid < C::G * C::R;
+    int wsub = 0, mu = 0, nu = 0;
+    if constexpr (C::OWN) {
+        wsub = __builtin_amdgcn_readfirstlane(tid / C::R);
+        live = tid % C::R < C::ROWS;
+        mu = live ? tid % C::R / L : 0;
+        nu = live ? tid % C::R % L : 0;
+    } else if (pair) {
+        const int i = tid % C::PAIR;
+        wsub = tid / C::PAIR;
+        mu = i / C::M * (L / 2);
+        nu = 1 + i % C::M;
+    } else if (live) {
+        const int i = (tid - NPR) % SINGLE;
+        wsub = (tid - NPR) / SINGLE;
+        mu = i < SELF ? i / C::REAL * (L / 2) : 1 + (i - SELF) / L;
+        nu = i < SELF ? i % C::REAL * (L / 2) : (i - SELF) % L;
+    }
+    const int row = mu * L + nu;
     float wt[L / 2 + 1][3];
 #pragma unroll
     for (int om = 0; om <= L / 2; ++om)
 #pragma unroll
         for (int m = 0; m < 3; ++m) wt[om][m] = wgen[(row * L + om) * 3 + m];
+    if constexpr (!C::OWN)  // past the last row: zero
+        for (int i = tid; i < 2 * C::G * 3 * (C::ES - C::ROWS); i += NT)
+            e_s[i / (C::ES - C::ROWS) * C::ES + C::ROWS + i % (C::ES - C::ROWS)] = 0.f;
+
+    // the row of this thread in window w of the run: the magnitudes' weighted sums
+    auto row_sums = [&](int w, float (&m)[L], float (&e)[3]) __attribute__((always_inline)) {
+        const float2 *src = P + row * RS + S * w;
+        float2 b[L], f[L];
+#pragma unroll
+        for (int r = 0; r < L; ++r) b[r] = src[r];
+        sal_dft::cdft<L>(b, tw.w, f);
+        e[0] = e[1] = e[2] = 0.f;
+#pragma unroll
+        for (int om = 0; om < L; ++om) {
+            m[om] = __builtin_amdgcn_sqrtf(fmaf(f[om].x, f[om].x, f[om].y * f[om].y));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) e[c] = fmaf(wt[om <= L / 2 ? om : L - om][c], m[om], e[c]);
+        }
+    };
 
     for (int tile = blk; tile < ntile; tile += nblk) {
         const int kr = tile % nrun, k1 = (tile / nrun) % kd1, k0 = tile / (nrun * kd1);
@@ -326,61 +395,73 @@ __global__ __launch_bounds__(RunCfg<L>::NT) void k_energy_run(const float *__res
         }
         __syncthreads();
         // ---------------- stage C: DFT along y per row (mu, nu), projections -------------
-        for (int w = wfirst; w < cnt; w += wstep) {
-            const int win = tail ? min(w + wsub, cnt - 1) : w;
-            const float2 *src = P + row * RS + S * win;
-            float2 b[L], f[L];
+        float *const E_run = E + ((int64_t)((p0 - bx.fo0) / S) * K1 + (p1 - bx.fo1) / S) * K2 + (p2 - bx.fo2) / S;
+        if constexpr (C::OWN) {
+            for (int w = wsub; w < cnt; w += C::G) {
+                float m[L], e[3];
+                row_sums(w, m, e);
 #pragma unroll
-            for (int r = 0; r < L; ++r) b[r] = src[r];
-            sal_dft::cdft<L>(b, tw.w, f);
-            float e0 = 0.f, e1 = 0.f, e2 = 0.f;
-#pragma unroll
-            for (int om = 0; om < L; ++om) {
-                const int k = om <= L / 2 ? om : L - om;
-                const float m = __builtin_amdgcn_sqrtf(fmaf(f[om].x, f[om].x, f[om].y * f[om].y));
-                e0 = fmaf(wt[k][0], m, e0);
-                e1 = fmaf(wt[k][1], m, e1);
-                e2 = fmaf(wt[k][2], m, e2);
+                for (int c = 0; c < 3; ++c) e[c] = live ? e[c] : 0.f;
+                // the block's tree: pairs 32, 16, 8, 4, 2, 1 lanes apart; rows of lanes: 0 holds
+                // component 0, 2 component 1, 1 and 3 component 2
+                const float a = row_sum(pair16(pair32(e[0], e[1]), pair32(e[2], e[2])));
+                if ((lane & 15) == 0 && lane < 48)
+                    e_s[(w * 3 + (lane == 0 ? 0 : (lane == 32 ? 1 : 2))) * C::NB + wave % C::NB] = a;
             }
-            e0 = live ? e0 : 0.f;
-            e1 = live ? e1 : 0.f;
-            e2 = live ? e2 : 0.f;
-            // the tree of the block's 64 rows: pairs 32, 16, 8, 4, 2, 1 lanes apart (of the last
-            // block's windows, whose other rows are zero, the levels that are left)
-            if (C::G > 1 && tail) {
-                if (C::W == 32) {
-                    const float a = row_sum(pair16(e0, e1)), c = row_sum(pair16(e2, e2));
-                    // row 2 s of window s holds component 0, row 2 s + 1 component 1
-                    if ((lane & 15) == 0 && w + wsub < cnt) {
-                        red_s[rb][win][(lane >> 4) & 1] = a;
-                        if ((lane & 16) == 0) red_s[rb][win][2] = c;
-                    }
-                } else {
-                    const float a = row_sum(e0), b1 = row_sum(e1), c = row_sum(e2);
-                    if ((lane & 15) == 0 && w + wsub < cnt) {
-                        red_s[rb][win][0] = a;
-                        red_s[rb][win][1] = b1;
-                        red_s[rb][win][2] = c;
-                    }
-                }
-            } else {
-                // rows of lanes: 0 holds component 0, 2 component 1, 1 and 3 component 2
-                const float a = row_sum(pair16(pair32(e0, e1), pair32(e2, e2)));
-                if ((lane & 15) == 0 && lane < 48) red_s[rb][win][lane == 0 ? 0 : (lane == 32 ? 1 : 2)] = a;
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < 3 * run; i += NT) {
-            const int m = i / run, w = i - m * run;
-            if (w < cnt) {
+            __syncthreads();
+            for (int i = tid; i < 3 * cnt; i += NT) {
                 float s = 0.f;
 #pragma unroll
-                for (int k = 0; k < C::NB; ++k) s += red_s[k][w][m];
-                const int64_t o = ((int64_t)((p0 - bx.fo0) / S) * K1 + (p1 - bx.fo1) / S) * K2 + (p2 - bx.fo2) / S + w;
-                E[m * nfr + o] = s;
+                for (int k = 0; k < C::NB; ++k) s += e_s[i * C::NB + k];
+                E_run[i % 3 * nfr + i / 3] = s;
+            }
+            continue;
+        }
+        int ck = 0;
+        for (int w0 = 0; w0 < cnt; w0 += C::G, ++ck) {
+            float *const es = e_s + (ck & 1) * (C::G * 3 * C::ES);
+            if (live && w0 + wsub < cnt) {
+                float m[L], e[3];
+                row_sums(w0 + wsub, m, e);
+                float *o = es + wsub * 3 * C::ES + row;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) o[c * C::ES] = e[c];
+                if (pair) {  // the row L - nu: the magnitudes in the other order
+                    o += L - 2 * nu;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        float s = 0.f;
+#pragma unroll
+                        for (int om = 0; om < L; ++om) s = fmaf(wt[om <= L / 2 ? om : L - om][c], m[om ? L - om : 0], s);
+                        o[c * C::ES] = s;
+                    }
+                }
+            }
+            __syncthreads();
+            // the rows' tree, 64 to a block, pairs 32, 16, 8, 4, 2, 1 apart: four lanes per window
+            // and component, by one wave while the others go on (into the other half of e_s)
+            if (wave == ck % C::NWV) {
+                for (int it = lane >> 2; it < C::G * 3; it += 16) {
+                    const float *src = es + it * C::ES + (lane & 3);
+                    float s = 0.f;
+#pragma unroll 1
+                    for (int k = 0; k < C::NB; ++k, src += 64) {
+                        float x[16];
+#pragma unroll
+                        for (int q = 0; q < 16; ++q) x[q] = src[4 * q];
+#pragma unroll
+                        for (int d = 8; d >= 1; d >>= 1)
+#pragma unroll
+                            for (int q = 0; q < d; ++q) x[q] += x[q + d];
+                        s += quad_sum(x[0]);
+                    }
+                    const int w = w0 + it / 3;
+                    if ((lane & 3) == 0 && w < cnt) E_run[it % 3 * nfr + w] = s;
+                }
             }
         }
-        // (the next run's stage A may write P now; red_s is rewritten two barriers later)
+        // the next run's stage A may write P (every read of it lies before the last barrier), and
+        // its stages' barriers separate the last two trees from the next writes of e_s
     }
     // max |V| of everything this workgroup read (all of it lies in the volume)
 #pragma unroll
@@ -624,19 +705,28 @@ int64_t win_blocks(int64_t nwin, int64_t nbox)
 }
 
 // Windows per run of k_energy_run for a box of kd windows, or 0 where P would not leave room
-// for two workgroups on a CU (wide strides of the largest cubes).  At most 32, less where P is
-// too large or the runs would not give every CU two workgroups; then the runs of a row are
-// made equal (rounded up to the windows the waves take together): at cube 18 on
-// 61 x 87 x 101 rows of 3 x 32 + 5 windows took 3.27 ms, of 26 + 26 + 26 + 23 2.79 ms.
+// for two workgroups on a CU (wide strides of the largest cubes).  About 32, less where P is
+// too large or the runs would not give every CU two workgroups, in multiples of the windows
+// transformed together; then the runs of a row are made equal: at cube 18 on 61 x 87 x 101 rows
+// of 3 x 32 + 5 windows took 3.27 ms, of 26 + 26 + 26 + 23 2.79 ms.
+template <int L>
+size_t run_lds(int S, int run)
+{
+    return (size_t)RunCfg<L>::ROWS * run_row_stride(L, S, run) * sizeof(float2);
+}
+template <int L>
+constexpr size_t run_lds_static = (RunCfg<L>::NE + RunCfg<L>::NWV) * sizeof(float);
+
 template <int L>
 int run_length(int S, int64_t kd0, int64_t kd1, int64_t kd2, int64_t nbox)
 {
-    auto lds = [&](int run) { return RunCfg<L>::ROWS * run_row_stride(L, S, run) * (int)sizeof(float2); };
-    int run = RunCfg<L>::MAXRUN;
-    while (run > 8 && (lds(run) > RUN_LDS_MAX || kd0 * kd1 * ((kd2 + run - 1) / run) * nbox < 512)) run >>= 1;
-    if (lds(run) > RUN_LDS_MAX) return 0;
-    const int64_t nrun = (kd2 + run - 1) / run, eq = (kd2 + nrun - 1) / nrun, wb = RunCfg<L>::WB;
-    return (int)((eq + wb - 1) / wb * wb);
+    constexpr int G = RunCfg<L>::G;
+    const size_t most = RUN_LDS_MAX - run_lds_static<L>;
+    int run = (RunCfg<L>::MAXRUN + G - 1) / G * G;
+    while (run - G >= 8 && (run_lds<L>(S, run) > most || kd0 * kd1 * ((kd2 + run - 1) / run) * nbox < 512)) run -= G;
+    if (run_lds<L>(S, run) > most) return 0;
+    const int64_t nrun = (kd2 + run - 1) / run, eq = (kd2 + nrun - 1) / nrun;
+    return (int)((eq + G - 1) / G * G);
 }
 
 template <int L>
@@ -644,21 +734,21 @@ hipError_t launch_run_L(const sal_ctx *c, const float *V, int64_t n0, int64_t n1
                         float *E, float *vmax_part, int *nparts, hipStream_t s, int nbox)
 {
     const int64_t ntile = (int64_t)((bx.d0 + S - 1) / S) * ((bx.d1 + S - 1) / S) * (((bx.d2 + S - 1) / S + run - 1) / run);
-    const size_t lds = (size_t)RunCfg<L>::ROWS * run_row_stride(L, S, run) * sizeof(float2);
+    const size_t lds = run_lds<L>(S, run), lds_all = lds + run_lds_static<L>;
     int64_t nb;
     if (bx.table) {
         bx.per_box = (int)(ntile < WIN_PER_BOX ? ntile : WIN_PER_BOX);
         nb = (int64_t)bx.per_box * nbox;
     } else {
         // at most WIN_BLOCKS workgroups (one partial each), in whole rounds of what 256 CUs hold
-        const int64_t fit = 256 * (160 * 1024 / (lds + 2048) < 8 ? 160 * 1024 / (lds + 2048) : 8);
+        const int64_t fit = 256 * (160 * 1024 / lds_all < 8 ? 160 * 1024 / lds_all : 8);
         nb = fit * (WIN_BLOCKS / fit);
         if (ntile < nb) nb = ntile;
     }
     if (nparts) *nparts = (int)nb;
     WinTw<L> tw;
     for (int k = 0; k < L; ++k) tw.w[k] = make_float2(c->tw_host[2 * k], c->tw_host[2 * k + 1]);
-    if (lds > 65536)
+    if (lds_all > 65536)
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_energy_run<L>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k_energy_run<L>, dim3((unsigned)nb), dim3(RunCfg<L>::NT), lds, s, V, (int)n0, (int)n1, (int)n2, bx,
