@@ -773,25 +773,42 @@ __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in
     }
 }
 
-// grad[j] += sum over partials (fixed order: one after the other, with 16 loads in flight).  A
-// step reads 32 MB of partials for a 24 -> 24 layer, through 244 waves (61 workgroups of four
-// and one load at a time took 122 us, 14 us so).
-__global__ __launch_bounds__(64) void k_sum_partials(const float *__restrict__ part, int nparts,
-                                                     int npar, float *__restrict__ grad)
+// grad[j] += sum over partials (fixed order: one after the other).  Bound by the latency of the
+// partials: a 24 -> 24 layer has 32 MB of them for its 15,576 sums, 244 waves' worth.  Four waves
+// per 64 sums bring 4 SPB partials at a time into LDS, all their loads in flight, and the first
+// adds them up.  Per layer: 61 workgroups of four waves with one load in flight at a time 122 us, one
+// wave per 64 sums with 16 loads in flight 14.6 us, this 9.3 us.
+constexpr int SPB = 32;
+__global__ __launch_bounds__(256) void k_sum_partials(const float *__restrict__ part, int nparts,
+                                                      int npar, float *__restrict__ grad)
 {
-    const int j = blockIdx.x * 64 + threadIdx.x;
-    if (j >= npar) return;
-    float s = 0.f;
-    int p = 0;
-    for (; p + 16 <= nparts; p += 16) {
-        float v[16];
+    __shared__ float buf[2][4 * SPB][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
+    const float *src = part + (j < npar ? j : npar - 1);
+    float v[SPB], s = 0.f;
+    auto load = [&](int p0) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = part[(int64_t)(p + i) * npar + j];
+        for (int i = 0; i < SPB; ++i) {
+            const int p = p0 + wave * SPB + i;
+            v[i] = src[(int64_t)(p < nparts ? p : nparts - 1) * npar];
+        }
+    };
+    load(0);
+    for (int p0 = 0, b = 0; p0 < nparts; p0 += 4 * SPB, b ^= 1) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s += v[i];
+        for (int i = 0; i < SPB; ++i) buf[b][wave * SPB + i][lane] = v[i];
+        __syncthreads();
+        if (p0 + 4 * SPB < nparts) load(p0 + 4 * SPB);
+        if (wave == 0) {
+            const int n = nparts - p0 < 4 * SPB ? nparts - p0 : 4 * SPB;
+            int i = 0;
+            for (; i + 16 <= n; i += 16)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) s += buf[b][i + q][lane];
+            for (; i < n; ++i) s += buf[b][i][lane];
+        }
     }
-    for (; p < nparts; ++p) s += part[(int64_t)p * npar + j];
-    grad[j] += s;
+    if (wave == 0 && j < npar) grad[j] += s;
 }
 
 // Masked mean squared error: dY = 2 (Y - T) / count on voxels at least `margin` from every
@@ -1056,7 +1073,7 @@ void wgrad(sal_net *n, int l, const void *in, const void *dz, int64_t nb, int64_
     hipLaunchKernelGGL((k_conv3_wgrad<CI, CO, F32>), dim3(grid), dim3(512), 0, s, in, dz, (int)nb, (int)n0,
                        (int)n1, (int)n2, part);
     const int npar = CO * 27 * CI + CO;
-    hipLaunchKernelGGL(k_sum_partials, dim3((npar + 63) / 64), dim3(64), 0, s, part, grid, npar,
+    hipLaunchKernelGGL(k_sum_partials, dim3((npar + 63) / 64), dim3(256), 0, s, part, grid, npar,
                        n->gr + n->woff[l]);
 }
 
