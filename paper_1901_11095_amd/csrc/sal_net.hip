@@ -13,6 +13,7 @@
 // a zero-padded convolution with the flipped, transposed kernel, run by the same kernel.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -877,14 +878,26 @@ __global__ __launch_bounds__(256) void k_adam(float *__restrict__ p, float *__re
     gr[i] = 0.f;
 }
 
-// Operand tables of one layer from the FP32 master, in BF16 and in FP32 (the FP32-operand
+struct prep_layer {
+    const float *W;
+    int ci, co, fwd_rows, fwd_k, bwd_rows, bwd_k;
+    uint16_t *fwd, *bwd;
+    float *fwd32, *bwd32;
+};
+struct prep_args {
+    prep_layer l[NL];
+};
+
+// Operand tables of layer blockIdx.y from the FP32 master, in BF16 and in FP32 (the FP32-operand
 // mode): forward [rows][ksteps*32] and the flipped/transposed kernel of the input-gradient
-// conv.
-__global__ __launch_bounds__(256) void k_prep_tables(const float *__restrict__ W, int ci, int co,
-                                                     uint16_t *__restrict__ fwd, float *__restrict__ fwd32,
-                                                     int fwd_rows, int fwd_k, uint16_t *__restrict__ bwd,
-                                                     float *__restrict__ bwd32, int bwd_rows, int bwd_k)
+// conv.  Launch-bound: a launch per layer took 22 us of a training step, one for all 4.3 us.
+__global__ __launch_bounds__(256) void k_prep_tables(prep_args args)
 {
+    const prep_layer &a = args.l[blockIdx.y];
+    const float *__restrict__ W = a.W;
+    const int ci = a.ci, co = a.co, fwd_rows = a.fwd_rows, fwd_k = a.fwd_k, bwd_rows = a.bwd_rows, bwd_k = a.bwd_k;
+    uint16_t *__restrict__ fwd = a.fwd, *__restrict__ bwd = a.bwd;
+    float *__restrict__ fwd32 = a.fwd32, *__restrict__ bwd32 = a.bwd32;
     const int i = blockIdx.x * 256 + threadIdx.x;
     // forward: row co, K index = tap * pad8(ci) + c (ci > 1) or tap (ci == 1).  The BF16 table
     // of the 24-channel layers is in the paired-row order of k_conv3: K index 32 s + 8 g + e
@@ -962,13 +975,14 @@ int bwd_k(int l) { return ksteps(CH[l + 1]) * 32; }
 
 hipError_t prep_tables(sal_net *n, hipStream_t s)
 {
+    prep_args a;
+    int most = 0;
     for (int l = 0; l < NL; ++l) {
-        const int nf = fwd_rows(l) * fwd_k(l), nbk = l > 0 ? bwd_rows(l) * bwd_k(l) : 0;
-        const int tot = nf > nbk ? nf : nbk;
-        hipLaunchKernelGGL(k_prep_tables, dim3((tot + 255) / 256), dim3(256), 0, s, n->p + n->woff[l],
-                           CH[l], CH[l + 1], n->fwd[l], n->fwd32[l], fwd_rows(l), fwd_k(l),
-                           l > 0 ? n->bwd[l] : nullptr, l > 0 ? n->bwd32[l] : nullptr, bwd_rows(l), bwd_k(l));
+        a.l[l] = {n->p + n->woff[l], CH[l], CH[l + 1], fwd_rows(l), fwd_k(l), bwd_rows(l), l > 0 ? bwd_k(l) : 0,
+                  n->fwd[l], l > 0 ? n->bwd[l] : nullptr, n->fwd32[l], l > 0 ? n->bwd32[l] : nullptr};
+        most = std::max({most, fwd_rows(l) * fwd_k(l), l > 0 ? bwd_rows(l) * bwd_k(l) : 0});
     }
+    hipLaunchKernelGGL(k_prep_tables, dim3((most + 255) / 256, NL), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
