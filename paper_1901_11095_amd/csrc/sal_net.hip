@@ -541,8 +541,189 @@ __global__ __launch_bounds__(conv_threads(CO)) void k_conv3(const void *__restri
 
 }
 
+// Which walk a workgroup of the weight gradient takes: the tiles that carry a gradient recur with
+// the blocks' period (16 tiles for 16^3), so consecutive walks go to one XCD (each then has whole
+// blocks), shifted by half a period from one round over its CUs to the next.
+__device__ __forceinline__ int wgrad_walk()
+{
+    int wg = blockIdx.x;
+    if ((gridDim.x & 511) == 0) {
+        const int i = wg >> 3, per = gridDim.x >> 3;
+        wg = (wg & 7) * per + (i & ~31) + ((i + 8 * (i >> 5)) & 31);
+    }
+    return wg;
+}
+
 // ------------------------------------------------------------------------------------
-// Weight and bias gradient of one layer: dW[co][k][ci] = sum_v dz[v][co] in[refl(v+k-1)][ci],
+// Weight and bias gradient of a layer with 24 BF16 input channels (the FP32-operand mode and the
+// one-channel layer take k_conv3_wgrad below): dW[co][k][ci] = sum_v dz[v][co] in[refl(v+k-1)][ci],
+// db[co] = sum_v dz[v][co].  BF16 16x16x32 MFMA, whose products of BF16 values are exact and
+// whose sums are FP32, with M = co, N = ci, K = two rows of 16 voxels along w.  K runs over
+// voxels, so both operands lie channel by channel in LDS ([ci][position], [co][voxel], two
+// positions packed per write): a lane reads its eight voxels of a channel in one piece, and the
+// ten positions that the taps dw = 0, 1, 2 of one (dt, du) need make three operands in registers.
+// A unit is one (dt, du) with channels 0..15, or channels 16..23 of two (dt, du): 14 units, two
+// per wave.  Each workgroup walks a fixed stride of tiles and writes its own partial sums
+// (summed afterwards in a fixed order: deterministic).  A K step without a nonzero dz is passed
+// over as in k_conv3_wgrad.  Batch of 64 16^3 blocks, 24 -> 24 channels, layers 4, 3 and 2: on FP32
+// MFMA 53, 88 and 99 us, so 23, 24 and 26 us;
+// gradients of layer 2 against FP64 from the same activations: RMS error 3.2e-7 either way (the FP32
+// sums').
+template <int CO>
+__global__ __launch_bounds__(512) void k_conv3_wgrad16(const uint16_t *__restrict__ in, const uint16_t *__restrict__ dz,
+                                                       int nb, int n0, int n1, int n2, float *__restrict__ part)
+{
+    constexpr int CI = 24, MT = (CO + 15) / 16, NV = TT * TU * TW, NPAR = CO * 27 * CI + CO;
+    static_assert(TW == 16 && TU % 2 == 0 && NV % 32 == 0 && NV / 32 <= 32, "K steps of two rows of 16 voxels");
+    constexpr int RW = 24;                            // positions' row stride: 16-byte reads
+    constexpr int CS = ((TT + 2) * PU * RW / 2 + 63) / 64 * 128 + 8;  // channel stride: 4 banks apart
+    constexpr int VS = NV + 8;                        // dz channel stride: 4 banks apart
+    constexpr int UNITS = 14, NPP = PW / 2;
+    static_assert(PW % 2 == 0 && PW <= RW, "pairs of positions");
+    __shared__ __attribute__((aligned(16))) uint16_t tin[CI * CS];
+    __shared__ __attribute__((aligned(16))) uint16_t tdz[16 * MT * VS];
+    __shared__ uint32_t live_s;  // bit q: some dz of the voxels 32q .. 32q + 31 is not zero
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, n = lane & 15;
+    const int ntw = (n2 + TW - 1) / TW, ntu = (n1 + TU - 1) / TU, ntt = (n0 + TT - 1) / TT;
+    const int ntiles = nb * ntt * ntu * ntw;
+    const int64_t vol = (int64_t)n0 * n1 * n2;
+
+    // this lane's (dt, du) and channel in the wave's units, and where its operands start
+    int uk[2], uc[2], ub[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int u = wave + 8 * a;
+        uk[a] = u < 9 ? u : 2 * (u - 9) + (n >> 3);
+        uc[a] = u < 9 ? n : 16 + (n & 7);
+        const int k = uk[a] < 9 ? uk[a] : 8;
+        ub[a] = uc[a] * CS + ((k / 3) * PU + k % 3 + (g >> 1)) * RW + 8 * (g & 1);
+    }
+    f4 acc[2][3][MT];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int dw = 0; dw < 3; ++dw)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[a][dw][mt] = f4{0.f, 0.f, 0.f, 0.f};
+    float dbias = 0.f;
+    for (int i = threadIdx.x; i < (16 * MT - CO) * VS; i += 512) tdz[CO * VS + i] = 0;  // rows past CO
+    auto inf_or_nan = [](uint32_t v) {  // two BF16 values
+        return (((v & 0x7fff7fffu) + 0x00800080u) & 0x80008000u) != 0u;
+    };
+
+    const int wg = wgrad_walk();
+    for (int tile = wg; tile < ntiles; tile += gridDim.x) {
+        int bid = tile;
+        const int tw_ = bid % ntw;
+        bid /= ntw;
+        const int tu_ = bid % ntu;
+        bid /= ntu;
+        const int tt_ = bid % ntt;
+        const int b = bid / ntt;
+        const int t0 = tt_ * TT, u0 = tu_ * TU, w0 = tw_ * TW;
+        __syncthreads();
+        if (threadIdx.x == 0) live_s = 0u;
+        bool odd = false;  // an infinity or a NaN among this thread's inputs
+        // channels 8 ch .. 8 ch + 7 of two positions or voxels next to each other, transposed
+        auto put = [](uint16_t *d, int stride, const u32x4 &v0, const u32x4 &v1) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                *reinterpret_cast<uint32_t *>(d + 2 * e * stride) = (v0[e] & 0xffffu) | (v1[e] << 16);
+                *reinterpret_cast<uint32_t *>(d + (2 * e + 1) * stride) = (v0[e] >> 16) | (v1[e] & 0xffff0000u);
+            }
+        };
+        for (int i = threadIdx.x; i < (TT + 2) * PU * NPP * 3; i += 512) {
+            const int pr = i / 3, ch = i - 3 * pr, row = pr / NPP, pw = 2 * (pr - row * NPP);
+            const int64_t line =
+                b * vol + ((int64_t)refl_idx(t0 - 1 + row / PU, n0) * n1 + refl_idx(u0 - 1 + row % PU, n1)) * n2;
+            const u32x4 v0 = *reinterpret_cast<const u32x4 *>(in + (line + refl_idx(w0 - 1 + pw, n2)) * CI + 8 * ch);
+            const u32x4 v1 = *reinterpret_cast<const u32x4 *>(in + (line + refl_idx(w0 + pw, n2)) * CI + 8 * ch);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) odd |= inf_or_nan(v0[e]) | inf_or_nan(v1[e]);
+            put(tin + 8 * ch * CS + row * RW + pw, CS, v0, v1);
+        }
+        __syncthreads();  // live_s is zero
+        auto vox = [&](int vv, int64_t *gi) {
+            const int gt = t0 + vv / (TU * TW), gu = u0 + (vv / TW) % TU, gw = w0 + vv % TW;
+            *gi = b * vol + ((int64_t)gt * n1 + gu) * n2 + gw;
+            return gt < n0 && gu < n1 && gw < n2;
+        };
+        if constexpr (CO == 24) {
+            for (int i = threadIdx.x; i < NV / 2 * 3; i += 512) {
+                const int vv = 2 * (i / 3), ch = i % 3;
+                u32x4 v[2] = {u32x4{0u, 0u, 0u, 0u}, u32x4{0u, 0u, 0u, 0u}};
+                uint32_t any = 0u;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    int64_t gi;
+                    if (vox(vv + h, &gi)) v[h] = *reinterpret_cast<const u32x4 *>(dz + gi * CO + 8 * ch);
+                    any |= v[h][0] | v[h][1] | v[h][2] | v[h][3];
+                }
+                put(tdz + 8 * ch * VS + vv, VS, v[0], v[1]);
+                if (any & 0x7fff7fffu) atomicOr(&live_s, 1u << (vv >> 5));
+            }
+        } else {
+            for (int i = threadIdx.x; i < NV * CO; i += 512) {
+                const int vv = i / CO, c = i - vv * CO;
+                int64_t gi;
+                const uint16_t v = vox(vv, &gi) ? dz[gi * CO + c] : (uint16_t)0;
+                tdz[c * VS + vv] = v;
+                if (v & 0x7fffu) atomicOr(&live_s, 1u << (vv >> 5));
+            }
+        }
+        const bool all = __syncthreads_or(odd);
+        const uint32_t todo = __builtin_amdgcn_readfirstlane((int)(all ? ~0u : live_s));
+        // the bias gradient: one lane per channel of the last wave, which has one unit
+        if (threadIdx.x >= 448 && threadIdx.x < 448 + CO) {
+#pragma unroll 16
+            for (int vv = 0; vv < NV; ++vv) dbias += from_act<false>(tdz[(threadIdx.x - 448) * VS + vv]);
+        }
+        for (int ks = 0; ks < NV / 32; ++ks) {
+            if (!(todo >> ks & 1)) continue;
+            bf16x8 av[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                av[mt] = *reinterpret_cast<const bf16x8 *>(tdz + (16 * mt + n) * VS + 32 * ks + 8 * g);
+            const int row = (2 * ks / TU * PU + 2 * ks % TU) * RW;
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                if (wave + 8 * a >= UNITS) continue;
+                const u32x4 d = *reinterpret_cast<const u32x4 *>(tin + ub[a] + row);
+                const uint32_t d4 = *reinterpret_cast<const uint32_t *>(tin + ub[a] + row + 8);
+                const u32x4 bv[3] = {d,
+                                     u32x4{__builtin_amdgcn_alignbit(d[1], d[0], 16), __builtin_amdgcn_alignbit(d[2], d[1], 16),
+                                           __builtin_amdgcn_alignbit(d[3], d[2], 16), __builtin_amdgcn_alignbit(d4, d[3], 16)},
+                                     u32x4{d[1], d[2], d[3], d4}};
+#pragma unroll
+                for (int dw = 0; dw < 3; ++dw)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[a][dw][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            av[mt], __builtin_bit_cast(bf16x8, bv[dw]), acc[a][dw][mt], 0, 0, 0);
+            }
+        }
+    }
+    float *pp = part + (int64_t)wg * NPAR;
+    if (threadIdx.x >= 448 && threadIdx.x < 448 + CO) pp[CO * 27 * CI + threadIdx.x - 448] = dbias;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        if (wave + 8 * a >= UNITS || uk[a] >= 9) continue;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int co = 16 * mt + 4 * g + j;
+                if (co >= CO) continue;
+#pragma unroll
+                for (int dw = 0; dw < 3; ++dw) pp[(co * 27 + 3 * uk[a] + dw) * CI + uc[a]] = acc[a][dw][mt][j];
+            }
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// Weight and bias gradient of one layer of the FP32-operand mode, or of the one-channel layer (its
+// input is the FP32 volume): dW[co][k][ci] = sum_v dz[v][co] in[refl(v+k-1)][ci],
 // db[co] = sum_v dz[v][co].  FP32 16x16x4 MFMA with M = co, N = ci, K = 4 voxels along w.  Each
 // workgroup walks a fixed stride of tiles and writes its own partial sums (summed afterwards
 // in a fixed order: deterministic).
@@ -553,21 +734,18 @@ __global__ __launch_bounds__(conv_threads(CO)) void k_conv3(const void *__restri
 // inside the block, dz is zero on 3/4 (last layers) to 1/4 (first) of the voxels of 16^3 blocks,
 // and a K step of four zero dz adds +-0 to every sum, so it is passed over (unless the tile's
 // inputs hold an infinity or a NaN, whose product with zero counts).  The tiles stay in their
-// storage type in LDS (43 KB with BF16: the two workgroups a CU gets overlap their loads),
-// loaded 16 bytes a lane.  Batch of 64 16^3 blocks, 24 -> 24 channels: 228 us with one scalar
-// load and a division per value and every K step taken, 53, 88 and 99 us (layers 4 to 2) so.
+// storage type in LDS, loaded 16 bytes a lane.
 template <int CI, int CO, bool F32>
 __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in,
                                                      const void *__restrict__ dz_, int nb, int n0,
                                                      int n1, int n2, float *__restrict__ part)
 {
     using Act = typename ActT<F32>::type;
-    static_assert(CI == 1 || CI == 24, "taps share N tiles in the two layouts above");
-    using In = typename ActT<F32 || CI == 1>::type;  // the one-channel input is the FP32 volume
+    static_assert(CI == 1 || (CI == 24 && F32), "taps share N tiles in the two layouts above");
     const Act *dz = reinterpret_cast<const Act *>(dz_);
     constexpr int MT = (CO + 15) / 16, NKW = CI == 1 ? 1 : 4, NPR = NKW / 2;
     constexpr int NPAR = CO * 27 * CI + CO, NV = TT * TU * TW;
-    __shared__ __attribute__((aligned(16))) In tin[NPOS * CI];
+    __shared__ __attribute__((aligned(16))) float tin[NPOS * CI];
     __shared__ __attribute__((aligned(16))) Act tdz[NV * CO];
     __shared__ uint32_t live_s[2];  // bit q: some dz of the voxels 4q .. 4q + 3 is not zero
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -601,18 +779,7 @@ __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in
         for (int q = 0; q < (NPR > 0 ? NPR : 1); ++q) accp[q][mt] = f4{0.f, 0.f, 0.f, 0.f};
     }
     float dbias = 0.f;
-    auto inf_or_nan = [](uint32_t v) {  // two BF16 values
-        return (((v & 0x7fff7fffu) + 0x00800080u) & 0x80008000u) != 0u;
-    };
-
-    // Which walk this workgroup takes: the tiles that carry a gradient recur with the blocks'
-    // period (16 tiles for 16^3), so consecutive walks go to one XCD (each then has whole
-    // blocks), shifted by half a period from one round over its CUs to the next.
-    int wg = blockIdx.x;
-    if ((gridDim.x & 511) == 0) {
-        const int i = wg >> 3, per = gridDim.x >> 3;
-        wg = (wg & 7) * per + (i & ~31) + ((i + 8 * (i >> 5)) & 31);
-    }
+    const int wg = wgrad_walk();
     for (int tile = wg; tile < ntiles; tile += gridDim.x) {
         int bid = tile;
         const int tw_ = bid % ntw;
@@ -637,18 +804,13 @@ __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in
                 tin[p] = v;
             }
         } else {
-            constexpr int CHK = CI / 8, NQ = F32 ? 2 : 1;  // chunks of 8 channels
+            constexpr int CHK = CI / 4;  // chunks of 4 channels
             for (int i = threadIdx.x; i < NPOS * CHK; i += 512) {
                 const int p = i / CHK, ch = i - p * CHK;
-                const u32x4 *q = reinterpret_cast<const u32x4 *>(reinterpret_cast<const Act *>(in) + src(p) * CI + 8 * ch);
-                u32x4 *d = reinterpret_cast<u32x4 *>(&tin[p * CI + 8 * ch]);
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const float *>(in) + src(p) * CI + 4 * ch);
 #pragma unroll
-                for (int k = 0; k < NQ; ++k) {
-                    const u32x4 v = q[k];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) odd |= F32 ? (v[e] & 0x7fffffffu) >= 0x7f800000u : inf_or_nan(v[e]);
-                    d[k] = v;
-                }
+                for (int e = 0; e < 4; ++e) odd |= (v[e] & 0x7fffffffu) >= 0x7f800000u;
+                *reinterpret_cast<u32x4 *>(&tin[p * CI + 4 * ch]) = v;
             }
         }
         __syncthreads();  // live_s is zero
@@ -702,18 +864,12 @@ __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in
             const uint32_t quads = (uint32_t)(todo >> (4 * row)) & 15u;
             if (!quads) continue;
             const int base = ((row / TU) * PU + row % TU) * PW + g;
-            const In *bsrc[NKW], *bpsrc[NPR > 0 ? NPR : 1];
+            const float *bsrc[NKW], *bpsrc[NPR > 0 ? NPR : 1];
 #pragma unroll
             for (int a = 0; a < NKW; ++a) bsrc[a] = tin + base * CI + off[a];
 #pragma unroll
             for (int q = 0; q < NPR; ++q) bpsrc[q] = tin + base * CI + offp[q];
             const Act *asrc = tdz + (16 * row + g) * CO + n;
-            auto bval = [](const In *p) {
-                if constexpr (CI == 1)
-                    return *p;
-                else
-                    return from_act<F32>(*p);
-            };
 #pragma unroll
             for (int w4 = 0; w4 < 4; ++w4) {
                 if (!(quads >> w4 & 1)) continue;
@@ -721,7 +877,7 @@ __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in
                 if constexpr (CI == 1) {
                     const int mt = wave & 1;
                     const float av = 16 * mt + n < CO ? from_act<F32>(asrc[ao + 16 * mt]) : 0.f;
-                    const float bv = 16 * (wave >> 1) + n < 27 ? bval(bsrc[0] + bo) : 0.f;
+                    const float bv = 16 * (wave >> 1) + n < 27 ? bsrc[0][bo] : 0.f;
                     acc[0][0] = mfma4(av, bv, acc[0][0]);
                 } else {
                     float av[MT];
@@ -730,11 +886,11 @@ __global__ __launch_bounds__(512) void k_conv3_wgrad(const void *__restrict__ in
                         av[mt] = (16 * mt + n < CO) ? from_act<F32>(asrc[ao + 16 * mt]) : 0.f;
 #pragma unroll
                     for (int q = 0; q < NPR; ++q) {
-                        const float b0 = bval(bsrc[2 * q] + bo), bp = bval(bpsrc[q] + bo);
+                        const float b0 = bsrc[2 * q][bo], bp = bpsrc[q][bo];
 #pragma unroll
                         for (int mt = 0; mt < MT; ++mt) acc[2 * q][mt] = mfma4(av[mt], b0, acc[2 * q][mt]);
                         if (wave + 8 * (2 * q + 1) < 27) {
-                            const float b1 = bval(bsrc[2 * q + 1] + bo);
+                            const float b1 = bsrc[2 * q + 1][bo];
 #pragma unroll
                             for (int mt = 0; mt < MT; ++mt) acc[2 * q + 1][mt] = mfma4(av[mt], b1, acc[2 * q + 1][mt]);
                         }
@@ -1084,8 +1240,12 @@ void wgrad(sal_net *n, int l, const void *in, const void *dz, int64_t nb, int64_
 {
     const int64_t tiles = conv_grid(nb, n0, n1, n2);
     const int grid = (int)(tiles < WG_BLOCKS ? tiles : WG_BLOCKS);
-    hipLaunchKernelGGL((k_conv3_wgrad<CI, CO, F32>), dim3(grid), dim3(512), 0, s, in, dz, (int)nb, (int)n0,
-                       (int)n1, (int)n2, part);
+    if constexpr (CI == 24 && !F32)
+        hipLaunchKernelGGL(k_conv3_wgrad16<CO>, dim3(grid), dim3(512), 0, s, (const uint16_t *)in, (const uint16_t *)dz,
+                           (int)nb, (int)n0, (int)n1, (int)n2, part);
+    else
+        hipLaunchKernelGGL((k_conv3_wgrad<CI, CO, F32>), dim3(grid), dim3(512), 0, s, in, dz, (int)nb, (int)n0,
+                           (int)n1, (int)n2, part);
     const int npar = CO * 27 * CI + CO;
     hipLaunchKernelGGL(k_sum_partials, dim3((npar + 63) / 64), dim3(256), 0, s, part, grid, npar,
                        n->gr + n->woff[l]);

@@ -376,3 +376,47 @@ def test_nonfinite_input_reaches_the_gradient(bad, prec):
     w = g[sw].reshape(24, 27)
     # tap 0 of the corner voxel's neighbours reads it, also for output voxels without gradient
     assert np.isnan(w).any()
+
+
+@pytest.mark.parametrize("nb,shape", [(1, (2, 2, 2)), (2, (4, 4, 16)), (3, (5, 7, 17)), (1, (9, 10, 33)), (40, (16, 16, 16))])
+def test_bf16_weight_gradient_of_the_layers(nb, shape):
+    """Weight and bias gradients of layers 2 (24 -> 24) and 5 (24 -> 3) against FP64 from the same
+    BF16 activations and gradients, read from the workspace (z1, a1 .. z4, a4, Y, dY, two gradient
+    buffers, each rounded up to 256 bytes; the first holds layer 2's at the end).  The products are
+    exact in FP32, so an element may be off by its longest chain of FP32 sums, 256 voxels of a tile
+    and one per tile, of half an ulp of the sum of its magnitudes each."""
+    g = torch.Generator().manual_seed(nb)
+    net = sal.Net(seed=3)
+    X = torch.randn((nb,) + shape, generator=g).cuda()
+    dY = torch.randn((nb,) + shape + (3,), generator=g).cuda()
+    net.forward(X)
+    net.grads(zero=True)
+    net.backward(X, dY)
+    G = torch.from_numpy(net.grads(zero=True)).double().cuda()
+    nv = X.numel()
+    ws = net.workspace(nb, shape, True)
+
+    def up(n):
+        return (n + 255) // 256 * 256
+
+    A = up(nv * 48)
+    dy = 8 * A + up(nv * 12)
+
+    def read(o, c):
+        return ws[o:o + nv * c * 2].view(torch.bfloat16).view((nb,) + shape + (c,)).double()
+
+    ch = (1, 24, 24, 24, 24, 3)
+    tiles = nb * -(-shape[0] // 4) * -(-shape[1] // 4) * -(-shape[2] // 16)
+    for layer, a, d in ((1, read(A, 24), read(dy + up(nv * 6), 24)), (4, read(7 * A, 24), read(dy, 3))):
+        co, off = ch[layer + 1], sum(ch[l + 1] * (27 * ch[l] + 1) for l in range(layer))
+        for axis, n in enumerate(shape):
+            i = torch.arange(-1, n + 1, device="cuda").abs()
+            a = a.index_select(axis + 1, torch.where(i >= n, 2 * (n - 1) - i, i))
+        D = d.reshape(-1, co).t().contiguous()
+        for k in range(27):
+            t, u, w = k // 9, k // 3 % 3, k % 3
+            P = a[:, t:t + shape[0], u:u + shape[1], w:w + shape[2]].reshape(-1, 24)
+            got = G[off:off + co * 27 * 24].view(co, 27, 24)[:, k]
+            assert bool(((got - D @ P).abs() <= (256 + tiles) * 2.0 ** -24 * (D.abs() @ P.abs())).all()), (layer, k)
+        bias = G[off + co * 27 * 24:off + co * (27 * 24 + 1)]
+        assert bool(((bias - D.sum(1)).abs() <= (256 + tiles) * 2.0 ** -24 * D.abs().sum(1)).all()), layer
