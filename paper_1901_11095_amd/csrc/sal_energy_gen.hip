@@ -85,16 +85,35 @@ __global__ __launch_bounds__(256) void k_energy_gen(const float *__restrict__ V,
 
     for (int i = tid; i < NW3; i += 256) wg_s[i] = wgen[i];
 
+    // This thread's samples of a plane and its positions of stage B, whose addresses are formed
+    // once: a reflection and two divisions per sample and plane, and a division per position and
+    // mu, were a twentieth of cube 5's instructions (whole pass on 256 x 512 x 512 voxels 2.42 -> 2.31 ms).
+    constexpr int NLP = (NP + 255) / 256, NJ = (NX * PY + 255) / 256;
+    uint32_t goff[NLP];
+    int boff[NJ];
+#pragma unroll
+    for (int i = 0; i < NLP; ++i) {
+        const int p = tid + 256 * i, xp = p / PY, yp = p - xp * PY;
+        goff[i] = p < NP ? (uint32_t)(refl_idx(x_base - H + xp, n1) * n2 + refl_idx(y_base - H + yp, n2)) : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) {
+        const int j = tid + 256 * i;
+        boff[i] = S * (j / PY) * PY + j % PY;
+    }
+
     float vmax = 0.f;
     auto load_plane = [&](int tv) {
         const int slot = ((tv % L) + L) % L;
-        const int64_t gt = refl_idx(tv, n0);
-        for (int p = tid; p < NP; p += 256) {
-            const int xp = p / PY, yp = p - xp * PY;
-            const int gx = refl_idx(x_base - H + xp, n1), gy = refl_idx(y_base - H + yp, n2);
-            const float v = V[gt * plane + (int64_t)gx * n2 + gy];
-            vmax = fmaxf(vmax, fabsf(v));
-            ring[slot][p] = v;
+        const float *src = V + refl_idx(tv, n0) * plane;
+#pragma unroll
+        for (int i = 0; i < NLP; ++i) {
+            const int p = tid + 256 * i;
+            if (p < NP) {
+                const float v = src[goff[i]];
+                vmax = fmaxf(vmax, fabsf(v));
+                ring[slot][p] = v;
+            }
         }
     };
     for (int k = 0; k < L - S; ++k) load_plane(t_begin - H + k);
@@ -119,11 +138,13 @@ __global__ __launch_bounds__(256) void k_energy_gen(const float *__restrict__ V,
 #pragma unroll 1
         for (int mu = 0; mu < h; ++mu) {
             // ---------------- stage B: DFT along x for this mu, all nu of a position ----
-            for (int j = tid; j < NX * PY; j += 256) {
-                const int yp = j % PY, xr = j / PY;
+#pragma unroll
+            for (int i = 0; i < NJ; ++i) {
+                const int j = tid + 256 * i;
+                if (j >= NX * PY) continue;
                 float2 a[L], f[L];
 #pragma unroll
-                for (int q = 0; q < L; ++q) a[q] = A_s[mu * NP + (S * xr + q) * PY + yp];
+                for (int q = 0; q < L; ++q) a[q] = A_s[mu * NP + boff[i] + q * PY];
                 sal_dft::cdft<L>(a, tw.w, f);
 #pragma unroll
                 for (int nu = 0; nu < L; ++nu) B_s[nu * (NX * PY) + j] = f[nu];
