@@ -53,7 +53,6 @@ __global__ __launch_bounds__(256) void k_energy_gen(const float *__restrict__ V,
     constexpr int NX = GenCfg<L>::NX, NY = GenCfg<L>::NY;
     // windows of x-rows and y-columns S apart (S = 2: the half-resolution lattice)
     constexpr int PX = S * (NX - 1) + L, PY = S * (NY - 1) + L, NP = PX * PY;
-    constexpr int NW3 = h * L * L * 3;
     __shared__ float ring[L][NP];
     // one plane per frequency: neighbouring lanes touch neighbouring values, so no bank is
     // asked twice.  Interleaved by frequency, a lane's stride of h or L complex values met the
@@ -61,7 +60,6 @@ __global__ __launch_bounds__(256) void k_energy_gen(const float *__restrict__ V,
     // 4, 6 and 7, with planes 181, 512 and 734 (cube 5, both strides odd: 267 either way).
     __shared__ float2 A_s[NP * h];
     __shared__ float2 B_s[NX * PY * L];
-    __shared__ float wg_s[NW3];
     __shared__ float red_s[4];
 
     const int tid = threadIdx.x;
@@ -82,8 +80,6 @@ __global__ __launch_bounds__(256) void k_energy_gen(const float *__restrict__ V,
     // E frame (the box itself unless a batch entry says otherwise)
     const int K1 = bx.fk1, K2 = bx.fk2;
     const int64_t nbox = (int64_t)bx.fk0 * K1 * K2;
-
-    for (int i = tid; i < NW3; i += 256) wg_s[i] = wgen[i];
 
     // This thread's samples of a plane and its positions of stage B, whose addresses are formed
     // once: a reflection and two divisions per sample and plane, and a division per position and
@@ -164,7 +160,9 @@ __global__ __launch_bounds__(256) void k_energy_gen(const float *__restrict__ V,
 #pragma unroll
                 for (int r = 0; r < L; ++r) b[r] = B_s[nu * (NX * PY) + x0 * PY + S * y0 + r];
                 sal_dft::cdft<L>(b, tw.w, f);
-                const float *w = &wg_s[(mu * L + nu) * L * 3];
+                // (uniform: scalar loads; from LDS five of the row's eight LDS reads were these, cube 5
+                // on 128 x 256 x 256 voxels 278 us, so 270)
+                const float *w = wgen + (mu * L + nu) * L * 3;
                 float m[L];
 #pragma unroll
                 for (int om = 0; om < L; ++om) m[om] = __builtin_amdgcn_sqrtf(fmaf(f[om].x, f[om].x, f[om].y * f[om].y));
