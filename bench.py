@@ -64,6 +64,18 @@ def slide_flops_per_voxel(L: int = 16) -> int:
     return 2 * L * L + 8 * L * L * (L // 2) + 8 * nb + 4 * nb + 6 * nb
 
 
+def slide_kernel_flops_per_voxel(L: int = 16) -> int:
+    """Flops per window as that kernel spends them: its update multiplies each plane bin by a
+    few constants instead of each stored bin by a twiddle (rows v = 4q + r: 0, 15, 5, 15 flops at
+    L = 16, 0, 5, 0, 5 at L = 8, and two adds per stored bin), and the bins kt and L - kt (beyond
+    the first eight ky also ky and -ky) share their weights, their magnitudes added first:
+    36,672 at L = 16, 4,848 at L = 8."""
+    nb, h = L ** 3 // 2, L // 2 + 1
+    products = (35 if L == 16 else 10) * L * L // 8
+    sums = 4 * L * (h - 2 + 6 * h) + (L - 8) * L // 4 * (7 * h + L - 2)
+    return 2 * L * L + 8 * L * L * (L // 2) + products + 2 * nb + 4 * nb + sums
+
+
 def pair_dft_flops(L: int) -> int:
     """Real flops of one L-point complex DFT with its terms and outputs in conjugate pairs
     (sums and differences of the inputs r and L - r times the real and imaginary twiddle
@@ -663,7 +675,7 @@ def survey_L8_leg(args, dev):
     ms, km = time_form(ctx, Vg, steps, 2)
     fpv = dft_flops_per_voxel(L)
     roof = roofline_block("k_energy_slide<%d, 1> (windows sliding along t)" % L, km["energy"], N,
-                          slide_flops_per_voxel(L), "f32_vector", "energy_slide_L%d_%s" % (L, name),
+                          slide_kernel_flops_per_voxel(L), "f32_vector", "energy_slide_L%d_%s" % (L, name),
                           "k_energy_slide", bound="alu")
     roof["direct_equivalent_tflops"] = fpv * N / (km["energy"] * 1e-3) / 1e12
     out = {"workload": name, "shape": list(V.shape), "L": L, "voxels_per_s": N / (ms * 1e-3),
@@ -766,14 +778,16 @@ def main(argv=None):
         # the windows slide along t: the flops of that method against the FP32 vector peak
         # (packed FP32 instructions are not used: 256 CUs x 4 SIMDs x 16 lanes x 2 x 2.4 GHz)
         roof = roofline_block("k_energy_slide<%d, 1> (windows sliding along t)" % args.L, kms["energy"], N,
-                              slide_flops_per_voxel(args.L), "f32_vector",
+                              slide_kernel_flops_per_voxel(args.L), "f32_vector",
                               "energy_slide_L%d_%s" % (args.L, args.workload), "k_energy_slide", bound="alu")
         roof["flops_convention"] = (
-            "per window: 2L^2 (packed real DFT along x of one position of the plane difference) + "
-            "8L^2 L/2 (complex DFT along y of the L/2 packed columns) + 8 per stored bin (complex "
-            "multiply-add of the update, L^3/2 bins) + 4 per bin (magnitude, square root as 1) + "
-            "6 per bin (three weighted sums) = %d; adds and square roots count one flop, so the "
-            "vector-issue use is higher than frac" % slide_flops_per_voxel(args.L))
+            "per window, as the kernel spends them: 2L^2 (packed real DFT along x of one position of "
+            "the plane difference) + 8L^2 L/2 (complex DFT along y of the L/2 packed columns) + the "
+            "update's products per plane bin + 2 per stored bin (L^3/2 bins) + 4 per bin (magnitude, "
+            "square root as 1) + the weighted sums of the bins that share weights = %d (%d with a "
+            "twiddle and three weights per stored bin); adds and square roots count one flop, so the "
+            "vector-issue use is higher than frac"
+            % (slide_kernel_flops_per_voxel(args.L), slide_flops_per_voxel(args.L)))
         roof["direct_equivalent_tflops"] = fpv * N / (kms["energy"] * 1e-3) / 1e12
     else:
         roof = roofline_block("k_energy_f32<%d>" % args.L, kms["energy"], N, fpv, "f32",
