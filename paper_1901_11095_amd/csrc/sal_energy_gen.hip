@@ -228,8 +228,8 @@ hipError_t launch_gen_L(const sal_ctx *c, const float *V, int64_t n0, int64_t n1
     int64_t nb;
     gen_grid<L>((bx.d0 + S - 1) / S, (bx.d1 + S - 1) / S, (bx.d2 + S - 1) / S, &nby, &nbx, &tt, &nb, nbox);
     if (bx.table) {
-        bx.per_box = (int)nb;
-        nb *= nbox;
+        bx.per_box = batch_per_box(nb);
+        nb = (int64_t)bx.per_box * nbox;
     }
     if (nparts) *nparts = (int)nb;
     if (nb == 0) return hipSuccess;

@@ -574,8 +574,8 @@ static hipError_t launch_slide_L(const sal_ctx *c, const float *V, int64_t n0, i
     int64_t nb = (int64_t)nseg * np * nbx * nby;
     if (nparts) *nparts = (int)nb;  // (a batch takes no partials)
     if (bx.table) {
-        bx.per_box = (int)nb;
-        nb *= nbox;
+        bx.per_box = batch_per_box(nb);
+        nb = (int64_t)bx.per_box * nbox;
     } else {
         nb = 8 * (((int64_t)nbx * nby + 7) / 8) * nseg * np;  // eight equal column ranges
     }

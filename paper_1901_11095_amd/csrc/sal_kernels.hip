@@ -1208,8 +1208,8 @@ static hipError_t launch_energy_L(const sal_ctx *c, const float *V, int64_t n0, 
     energy_grid<L>((bx.d0 + S - 1) / S, (bx.d1 + S - 1) / S, (bx.d2 + S - 1) / S, &nby, &nbx, &tt, &nb, nbox,
                    bx.table != nullptr);
     if (bx.table) {
-        bx.per_box = (int)nb;
-        nb *= nbox;
+        bx.per_box = batch_per_box(nb);
+        nb = (int64_t)bx.per_box * nbox;
     }
     if (nparts) *nparts = (int)nb;
     if (c->p.precision != SAL_FP32)
