@@ -1155,15 +1155,15 @@ __global__ __launch_bounds__(64) void k_project(const float2 *__restrict__ F, in
 // Steps of the t walk.  Every step stands alone, so a walk only amortises its workgroup's
 // start (the operand tables and the first samples, some 2 us of the 56 a step takes at cube
 // 16 in split BF16), while its length is the grain of the last round of workgroups, 512 or 768
-// at a time: 32 steps where they leave at least 16 rounds, shorter down to `least` (the
-// partials of a volume are sized for two steps a workgroup; batches of boxes take none).  The
-// tile checks of 10 and 26 tiles of 32^3 in split BF16 took 3.9 ms with walks of 8 (800 and
-// 2,080 workgroups: 2 and 5 rounds), 3.4 ms with walks of 2 and 4; 128 x 256 x 256 7.82 ->
-// 7.48 ms for the pass.
-static int tt_len_for(int64_t n0, int64_t tiles_xy, int64_t least)
+// at a time: 32 steps where they leave at least 16 rounds, shorter down to two (the partials of
+// a volume are sized for two steps a workgroup; 128 x 256 x 256 in split BF16 7.82 -> 7.48 ms
+// for the pass).  A batch takes no partials, and fewer than half of its workgroups have work (its
+// entries are tiles and slabs a sixth of them): twice as many, down to one step (tile checks of
+// 10, 26, 51 and 11 tiles of 32^3 7.4 ms with 8,192, 7.0 ms with 16,384).
+static int tt_len_for(int64_t n0, int64_t tiles_xy, bool batch)
 {
     int64_t tt = 32;
-    while (tt > least && tiles_xy * ((n0 + tt - 1) / tt) < 8192) tt >>= 1;
+    while (tt > (batch ? 1 : 2) && tiles_xy * ((n0 + tt - 1) / tt) < (batch ? 16384 : 8192)) tt >>= 1;
     return (int)tt;
 }
 
@@ -1175,7 +1175,7 @@ static void energy_grid(int64_t n0, int64_t n1, int64_t n2, int *nby, int *nbx, 
     using C = TileCfg<L>;
     *nby = (int)((n2 + C::TY - 1) / C::TY);
     *nbx = (int)((n1 + C::NW - 1) / C::NW);
-    *tt = tt_len_for(n0, (int64_t)(*nby) * (*nbx) * nbox, batch ? 1 : 2);
+    *tt = tt_len_for(n0, (int64_t)(*nby) * (*nbx) * nbox, batch);
     *nblk = (int64_t)(*nby) * (*nbx) * ((n0 + *tt - 1) / *tt);
 }
 
