@@ -43,7 +43,7 @@ constexpr int FT = 4, FW = 16, FPT = FT + 2, FPW = FW + 2;
 __host__ __device__ constexpr int conv_fu(int co) { return co >= 16 ? 8 : 4; }
 __host__ __device__ constexpr int conv_threads(int co) { return 64 * FT * conv_fu(co) / 4; }
 constexpr int WG_BLOCKS = 512;                          // workgroups of the weight-gradient pass
-constexpr unsigned CONV_BLOCKS = 2048;                  // persistent workgroups of a convolution
+constexpr unsigned CONV_BLOCKS = 2048;                  // persistent workgroups of a convolution, at most
 
 enum { MODE_REFLECT = 0, MODE_ZERO = 1 };
 enum { EPI_GELU = 0, EPI_LINEAR = 1, EPI_DGELU = 2 };
@@ -1195,9 +1195,15 @@ void conv(const void *in, int64_t nb, int64_t n0, int64_t n1, int64_t n2, const 
           const float *bias, const void *zprev, void *o0, void *o1, int64_t vs, int64_t cs,
           hipStream_t s, float3 oscale = make_float3(1.f, 1.f, 1.f))
 {
-    // persistent workgroups: a few per CU, each walking tiles with its weights in registers
+    // Persistent workgroups, each walking tiles with its weights in registers.  With 24 BF16 input
+    // channels as many as the chip holds at once, one or two per CU: more only load the weights
+    // and wait for a first tile again (24 -> 24 on 64 blocks of 16^3 29.0 us with a workgroup per
+    // tile, 23.6 with 256 for the 512 tiles; 130 x 150 x 170 222 and 183 us, 256^3 920 and 872;
+    // 24 -> 3 16.6 and 13.8, 123 and 115, 579 and 570).  The others' weights are few and their
+    // starts short: eight per CU balance better (1 -> 24 on 256^3 394 us, 647 with 256).
+    constexpr unsigned most = CI == 24 && !F32 ? (CO == 24 ? 256 : 512) : CONV_BLOCKS;
     const unsigned tiles = conv_tiles_fwd(CO, nb, n0, n1, n2);
-    const unsigned grid = tiles < CONV_BLOCKS ? tiles : CONV_BLOCKS;
+    const unsigned grid = tiles < most ? tiles : most;
     hipLaunchKernelGGL((k_conv3<CI, CO, MODE, EPI, F32>), dim3(grid), dim3(conv_threads(CO)), 0, s,
                        in, (int)nb, (int)n0, (int)n1, (int)n2, w, bias, zprev, o0, o1, vs, cs, oscale);
 }
