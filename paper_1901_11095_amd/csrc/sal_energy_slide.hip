@@ -33,7 +33,11 @@
 //     update; at output steps (every S-th window along t) their magnitudes are weighted into
 //     E_t, E_x, E_y.
 // With S > 1 every row still enters and leaves (the sums slide one row per step), while the
-// workgroups, the y positions and the magnitudes are those of the lattice windows only.
+// workgroups, the y positions and the magnitudes are those of the lattice windows only.  At cube
+// 16 stage 2 is then a larger part of the step and takes ky and -ky together: the cosine and sine
+// sums of both parts (16 rows for 16 ky, half the MFMAs) and eight additions.  Stride 4 on 512^3
+// 5.52 -> 5.00 ms for the pass; RMS error of E against FP64 at strides 2 to 7 0.96 to 1.02 times
+// what it was, 5.5e-8 to 9.6e-8.  S = 1 keeps one sum per row of P and its rounding.
 // In wave 0 the bins (kt, ky) and (-kt, -ky) of the packed column sit in one lane; its
 // update is applied to U = Z[k] + conj Z[-k] = 2 D_{kx=0}[k] and V = Z[k] - conj Z[-k] =
 // 2i D_{kx=L/2}[k] instead (the plane spectra transformed the same way), so every slot is one
@@ -82,6 +86,8 @@ struct SlideGeo {
     static constexpr int NS1 = (PY + 15) / 16;  // stage-1 blocks of 16 positions
     static constexpr int NLD = (L * PY + 64 * NW - 1) / (64 * NW);  // plane samples per thread
     static constexpr int RW = NS1 + 1 < NW ? NS1 + 1 : NW - 1;       // the wave storing E
+    static constexpr bool PAIR_Y = L == 16 && S > 1;                 // stage 2 in conjugate pairs
+    static constexpr int NA2 = PAIR_Y ? 1 : MT * KS2 / 4;            // its operands, by four K steps
     static_assert(16 * NS1 <= PLS && 2 * S < L, "tile geometry");
 };
 
@@ -206,7 +212,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
     __shared__ float vred_s[SNW];
     // constant A operands, per lane: stage 1 [lane][K step], stage 2 [K step / 4][lane][4]
     __shared__ float4 a1_s[64];
-    __shared__ float4 a2_s[MT * KS2 / 4][64];
+    __shared__ float4 a2_s[G::NA2][64];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, n = lane & 15;
@@ -267,6 +273,15 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
         }
         a1_s[lane] = a;
     }
+    if constexpr (G::PAIR_Y) {
+        // rows 4 q .. 4 q + 3: cos and sin of M tile 0's ky of lane group q (of ky = 0 and 8 the
+        // cosines), then of M tile 1's; K step t has the taps 4 t .. 4 t + 3
+        if (threadIdx.x < 64) {
+            const int j = n & 3, row = n == 1 ? 2 : n & 12, mt = j >> 1, im = n == 1 ? 0 : j & 1;
+            const float *w = w_s2 + (mt * KS2 + im) * 64 + (g << 4) + row;
+            a2_s[0][lane] = make_float4(w[0], w[2 * 64], w[4 * 64], w[6 * 64]);
+        }
+    } else
     for (int i = threadIdx.x; i < MT * KS2 * 16; i += 64 * SNW) {
         const int r = i >> 6, ln = i & 63;  // operands 4 r .. 4 r + 3 in the order (mt, kk)
         float4 a;
@@ -387,7 +402,22 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
         f4 acc[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] = f4{0.f, 0.f, 0.f, 0.f};
-        {
+        if constexpr (G::PAIR_Y) {
+            // cosine and sine sums of both parts, X of Re and Y of Im: P[+-ky] = (Cx +- Sy, Cy -+ Sx)
+            const float *src = s1_s[b] + (S * n + g) * S1S + 2 * wave;
+            const float4 w = a2_s[0][lane];
+            f4 X = f4{0.f, 0.f, 0.f, 0.f}, Y = X;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float2 x = *reinterpret_cast<const float2 *>(src + 4 * t * S1S);
+                const float wt = t == 0 ? w.x : (t == 1 ? w.y : (t == 2 ? w.z : w.w));
+                X = mfma4(wt, x.x, X);
+                Y = mfma4(wt, x.y, Y);
+            }
+            acc[0] = sp_lane ? f4{X[0], Y[0], X[1], Y[1]}
+                             : f4{X[0] + Y[1], Y[0] - X[1], X[0] - Y[1], Y[0] + X[1]};
+            acc[MT - 1] = f4{X[2] + Y[3], Y[2] - X[3], X[2] - Y[3], Y[2] + X[3]};
+        } else {
             const float *src = s1_s[b] + (S * n + g) * S1S + 2 * wave;
 #pragma unroll
             for (int kh = 0; kh < KS2 / 4; ++kh) {
