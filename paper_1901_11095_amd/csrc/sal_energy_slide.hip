@@ -35,8 +35,8 @@
 // With S > 1 every row still enters and leaves (the sums slide one row per step), while the
 // workgroups, the y positions and the magnitudes are those of the lattice windows only.  At cube
 // 16 stage 2 is then a larger part of the step and takes ky and -ky together: the cosine and sine
-// sums of both parts (16 rows for 16 ky, half the MFMAs) and eight additions.  Stride 4 on 512^3
-// 5.52 -> 5.00 ms for the pass; RMS error of E against FP64 at strides 2 to 7 0.96 to 1.02 times
+// sums of both parts (16 rows for 16 ky, half the MFMAs) and eight additions.  Energies of stride 4
+// on 512^3 4.38 -> 3.74 ms; RMS error of E against FP64 at strides 2 to 7 0.96 to 1.02 times
 // what it was, 5.5e-8 to 9.6e-8.  S = 1 keeps one sum per row of P and its rounding.
 // In wave 0 the bins (kt, ky) and (-kt, -ky) of the packed column sit in one lane; its
 // update is applied to U = Z[k] + conj Z[-k] = 2 D_{kx=0}[k] and V = Z[k] - conj Z[-k] =
