@@ -218,11 +218,9 @@ __global__ __launch_bounds__(256) void k_halo_copies(float *__restrict__ Eb, int
 // {min, max} of each raw map over one tile per workgroup; tiles numbered (t, x, y), y fastest.
 // A NaN in a tile makes its extremes -inf and +inf, so the check of the tiles that pass the
 // checked tiles' extremes always takes it.
-// One pass over the maps, bound by HBM (12 bytes a voxel); a volume has few tiles, so a tile
-// takes 16 waves with four voxels in flight per thread, whose position advances by carries
-// instead of divisions: 256^3 in tiles of 32, 83 us with four waves and a division per voxel,
-// 37 us.
-constexpr int TMT = 1024;
+// One pass over the maps, bound by HBM (12 bytes a voxel), TMT threads a tile with four voxels in
+// flight each, whose position advances by carries instead of divisions.
+template <int TMT>
 __global__ __launch_bounds__(TMT) void k_tile_minmax(const float *__restrict__ S, int n0, int n1, int n2, int tile,
                                                      int ntx, int nty, float *__restrict__ out)
 {
@@ -345,12 +343,23 @@ hipError_t launch_halo_copies(float *Eb, int64_t estride, const int *tiles, cons
     return hipGetLastError();
 }
 
+// A volume in large tiles has few of them: 16 waves each (256^3 in tiles of 64 473 us with four
+// waves and a division per voxel, 137 us with four, 65 us with 16; 128^3 in tiles of 32 38, 14 and
+// 11 us).  From 2^14 voxels on; smaller tiles are many, most of 16 waves would have nothing to load
+// and each tile still waits for them (256^3 in tiles of 4 414 us with four waves, 1,689 with 16; of
+// 8 119 and 234, of 24 59 and 58; 130 x 150 x 170 in tiles of 24 18 and 19).
+constexpr int64_t TILE_WIDE = 1 << 14;
+
 hipError_t launch_tile_minmax(const float *S_raw, int64_t n0, int64_t n1, int64_t n2, int tile, float *out,
                               hipStream_t s)
 {
     const int nt0 = (int)((n0 + tile - 1) / tile), nt1 = (int)((n1 + tile - 1) / tile),
               nt2 = (int)((n2 + tile - 1) / tile);
-    hipLaunchKernelGGL(k_tile_minmax, dim3((unsigned)nt0 * nt1 * nt2), dim3(TMT), 0, s, S_raw, (int)n0, (int)n1,
-                       (int)n2, tile, nt1, nt2, out);
+    const dim3 grid((unsigned)nt0 * nt1 * nt2);
+    const int64_t most = (n0 < tile ? n0 : tile) * (n1 < tile ? n1 : tile) * (n2 < tile ? n2 : tile);
+    if (most >= TILE_WIDE)
+        hipLaunchKernelGGL(k_tile_minmax<1024>, grid, dim3(1024), 0, s, S_raw, (int)n0, (int)n1, (int)n2, tile, nt1, nt2, out);
+    else
+        hipLaunchKernelGGL(k_tile_minmax<256>, grid, dim3(256), 0, s, S_raw, (int)n0, (int)n1, (int)n2, tile, nt1, nt2, out);
     return hipGetLastError();
 }
