@@ -737,7 +737,9 @@ hipError_t launch_run_L(const sal_ctx *c, const float *V, int64_t n0, int64_t n1
     const size_t lds = run_lds<L>(S, run), lds_all = lds + run_lds_static<L>;
     int64_t nb;
     if (bx.table) {
-        bx.per_box = (int)(ntile < WIN_PER_BOX ? ntile : WIN_PER_BOX);
+        // as window by window: a batch of one box has the chip to itself (a tile of 32^3 at cube 12
+        // and stride 3 checked in 68 us window by window, 88 in runs on 64 workgroups, 56 so)
+        bx.per_box = (int)(win_blocks(ntile, nbox) / nbox);
         nb = (int64_t)bx.per_box * nbox;
     } else {
         // at most WIN_BLOCKS workgroups (one partial each), in whole rounds of what 256 CUs hold

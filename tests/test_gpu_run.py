@@ -51,3 +51,19 @@ def test_box_and_batch_equal_whole_volume():
     for k, lo in enumerate(tiles):
         sl = (slice(None),) + tuple(slice(a, a + d) for a, d in zip(lo, td))
         assert torch.equal(X[k], Sr[sl]), lo
+
+
+@pytest.mark.parametrize("L,stride", [(9, 1), (10, 4), (12, 3), (18, 1), (20, 2)])
+def test_batch_of_one_and_of_two(L, stride):
+    """A lone tile takes as many workgroups as it has runs, a tile of a larger batch at most 64 (each
+    with several runs): both equal the box of the same voxels bit for bit."""
+    shape, td = (60, 61, 63), (26, 30, 33)
+    V = torch.from_numpy(synth.make_volume(shape, seed=L, n_faults=1, throw=2)).cuda()
+    ctx = sal.Saliency(L=L, stride=stride)
+    _, _, Sr, st = ctx.saliency_maps(V)
+    for tiles in ([(17, 15, 14)], [(0, 31, 30), (17, 15, 14)]):
+        X = torch.empty((len(tiles), 3) + td, dtype=torch.float32, device="cuda")
+        err = torch.zeros(len(tiles), dtype=torch.float32, device="cuda")
+        sal.check_tiles(ctx, V, tiles, Sr.clone(), tiles, td, st, 0.02, err, exact_out=X)
+        for k, lo in enumerate(tiles):
+            assert torch.equal(X[k], ctx.raw_box(V, lo, td)), (len(tiles), lo)
