@@ -1447,13 +1447,32 @@ hipError_t launch_project(const sal_ctx *c, const float *spectra, int64_t nvox, 
     return hipGetLastError();
 }
 
+// Whether Eq. (5) of a box of nb voxels runs on the tiled kernels, which read each E about 1.4
+// times, or on k_dcs_box, which reads one per ray and step; the sums run in one order in all of
+// them.  Tiled pays where many reads share a plane or the LDS offsets are constants:
+//   * the default axis rays up to r = 10 (k_dcs_axis): at every size (box of 64 x 256 x 320 at r = 8
+//     304 us with k_dcs_box, 43 us tiled; one of 8^3 4 us less, too); beyond, on large boxes (r = 12
+//     on 64 x 64 x 64 3 us more, on 64 x 96 x 128 4 us less, on 100 x 160 x 200 46 us of 376 less);
+//   * all six axis rays on every map, r >= 2, from 2^18 voxels (r = 4, whole call: six rays 32^3 38 us
+//     with k_dcs_box, 40 tiled, 64^3 57 and 49, 100 x 160 x 200 384 and 211; 26 rays 82 and 93, 141 and
+//     103, 1,239 and 852; at r = 1 26 rays on 100 x 160 x 200 451 and 571).
+// With fewer rays a map k_dcs_box is the faster one (t-x diagonals at r = 2 on 17 x 20 x 60 29 us, 41
+// tiled; on 100 x 160 x 200 218 and 303; one ray a map 5 us less on boxes below 10^5 voxels).
+static bool dcs_box_tiled(const sal_ctx *c, int64_t nb)
+{
+    if (dcs_tiled_lds_floats(c->p.rays, c->r) > DCS_LDS_MAX_FLOATS) return false;
+    if (c->p.rays[0] == (SAL_RAY_PT | SAL_RAY_MT) && c->p.rays[1] == (SAL_RAY_PX | SAL_RAY_MX) &&
+        c->p.rays[2] == (SAL_RAY_PY | SAL_RAY_MY))
+        return c->r <= 10 || nb >= (int64_t)1 << 20;
+    const uint32_t six = c->p.rays[0] & c->p.rays[1] & c->p.rays[2] & 63u;
+    return six == 63u && c->r >= 2 && nb >= (int64_t)1 << 18;
+}
+
 hipError_t launch_dcs_box(const sal_ctx *c, const float *Eb, const int64_t eo[3], const int64_t ed[3],
                           const int64_t n[3], const int64_t bo[3], const int64_t bd[3], float *S,
                           hipStream_t s)
 {
-    // the tiled kernels read each E about 1.4 times instead of once per ray and step; the sums run
-    // in one order in all of them (box of 64 x 256 x 320 at r = 8: 304 us with k_dcs_box, 43 us tiled)
-    if (dcs_tiled_lds_floats(c->p.rays, c->r) <= DCS_LDS_MAX_FLOATS) {
+    if (dcs_box_tiled(c, bd[0] * bd[1] * bd[2])) {
         auto i = [](const int64_t *v, int k) { return (int)v[k]; };
         const dcs_frame fr{i(eo, 0), i(eo, 1), i(eo, 2), i(ed, 0), i(ed, 1), i(ed, 2),
                            i(bo, 0), i(bo, 1), i(bo, 2), i(bd, 0), i(bd, 1), i(bd, 2)};

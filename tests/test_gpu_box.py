@@ -102,3 +102,24 @@ def test_raw_box_vs_oracle(L, rays, lo, dims):
     for m in range(3):
         err = np.abs(box[m] - ref[m]).max() / np.abs(ref[m]).max()
         assert err <= 1e-5, (m, err)
+
+
+@pytest.mark.parametrize("rays,d,dims", [
+    # either side of each line between the two forms of Eq. (5)
+    ("axis", 20, (9, 11, 13)), ("axis", 24, (9, 11, 13)), ("axis", 24, (64, 120, 137)), ("axis", 24, (64, 120, 136)),
+    ("six", 2, (64, 64, 64)), ("six", 4, (64, 64, 64)), ("six", 4, (63, 64, 65)), ("six", 8, (80, 66, 70)),
+    ("all26", 4, (64, 64, 64)), ("all26", 4, (63, 64, 65)), ("all26", 8, (80, 130, 140)),
+    ("tx", 4, (17, 20, 60)), ("tx", 8, (80, 130, 140)), ("mix", 8, (80, 130, 140)), ("perm", 4, (80, 130, 140))])
+def test_raw_box_forms_of_the_comparison(rays, d, dims):
+    """Every set of rays and size on either side of the rule that picks the kernel of Eq. (5) for a
+    box, against the same voxels of the whole volume bit for bit."""
+    masks = {"axis": sal.RAYS_AXIS, "six": sal.RAYS_ALL, "all26": (sal.RAY_ALL,) * 3, "tx": (sal.RAY_DIAG_TX,) * 3,
+             "mix": (sal.RAY_DIAG_TX | 3, sal.RAY_DIAG_TY | 12, sal.RAY_DIAG_XY | 48), "perm": (32, 1, 8)}[rays]
+    shape = (90, 130, 150)
+    print("box forms %s d=%d %s" % (rays, d, dims), flush=True)
+    V = torch.from_numpy(synth.make_volume(shape, seed=2, n_faults=1, throw=3)).cuda()
+    ctx = sal.Saliency(L=5, d=d, rays=masks)
+    _, _, Sr, _ = ctx.saliency_maps(V)
+    for lo in ((0, 0, 0), tuple(n - k for n, k in zip(shape, dims)), tuple((n - k) // 2 for n, k in zip(shape, dims))):
+        box = ctx.raw_box(V, lo, dims)
+        assert torch.equal(box, Sr[:, lo[0]:lo[0] + dims[0], lo[1]:lo[1] + dims[1], lo[2]:lo[2] + dims[2]]), lo
