@@ -187,11 +187,22 @@ __device__ __forceinline__ int box_tile(ebox &bx, int *v)
     return t - e * bx.per_box;
 }
 
-// Workgroups per entry of a batch whose largest entry has nb tiles: an odd number.  Workgroups go
-// round the eight XCDs, and a multiple of eight would give the same XCDs every small entry's few
-// tiles (the grid is the largest entry's): the checks of 98 tiles of 32^3 at cube 16 in split BF16, in
-// four calls, 9.0 ms with 48 to 384 workgroups per entry, 7.4 ms with one more.
-inline int batch_per_box(int64_t nb) { return (int)(nb | 1); }
+// Workgroups per entry of a batch whose largest entry has nb tiles.  Workgroups go round the eight
+// XCDs, and within one round its four shader engines, whichever is busy; an entry's tiles are the
+// first of its share of the grid (the largest entry's), the others leave at once.
+//   * An odd number: a multiple of eight would give the same XCDs every small entry's few tiles (the
+//     checks of 98 tiles of 32^3 at cube 16 in split BF16, in four calls, 9.0 ms with 48 to 384
+//     workgroups per entry, 7.4 ms with one more).
+//   * One that moves the next entry by 5 to 13 of the 32 places, either way: by one or three, the
+//     entries in flight leave the same places idle (80 tiles of 20 x 18 x 25 at cube 16, stride 4,
+//     841 us with 31 per entry, 545 with 37; 60 tiles of 16^3 at cube 16 2,166 and 1,776 us; split
+//     BF16 the same to 1 %).  At most nine more workgroups.
+inline int batch_per_box(int64_t nb)
+{
+    int64_t p = nb | 1;
+    for (int64_t m = p & 31; m < 5 || (m > 13 && m < 19) || m > 27; m = p & 31) p += 2;
+    return (int)p;
+}
 
 // ------------------------------------------------------------------ launchers
 // All return hipSuccess or the launch error.

@@ -227,3 +227,22 @@ def test_clustered_tiles_share_halos(L, prec, td):
             sl = (slice(None),) + tuple(slice(a, a + d) for a, d in zip(lo, td))
             assert torch.equal(X[k], Sr[sl]), (lo, k)
             assert torch.equal(P[sl], Sr[sl]), (lo, k)
+
+
+@pytest.mark.parametrize("L,kw", [(16, {"stride": 4}), (16, {}), (8, {}), (5, {}), (7, {"stride": 2}),
+                                  (16, {"precision": sal.BF16_SPLIT}), (8, {"t_direct": True})])
+@pytest.mark.parametrize("td", [(20, 18, 25), (1, 1, 1), (5, 24, 17)])
+def test_padded_workgroups_of_a_batch(L, kw, td):
+    """Entries of a batch get more workgroups than their largest has tiles (by one to nine): the rest
+    leave.  Lone and touching tiles against the box of the same voxels, bit for bit."""
+    V = torch.from_numpy(synth.make_volume((61, 58, 77), seed=L, n_faults=1, throw=3)).cuda()
+    ctx = sal.Saliency(L=L, **kw)
+    _, _, Sr, st = ctx.saliency_maps(V)
+    tiles = [(0, 0, 0), td, (61 - td[0], 58 - td[1], 77 - td[2]), (13, td[1], 9), (td[0], 0, td[2])]
+    for n in (1, 2, len(tiles)):
+        print("padded batch L=%d %s td=%s n=%d" % (L, kw, td, n), flush=True)
+        X = torch.empty((n, 3) + td, dtype=torch.float32, device="cuda")
+        err = torch.zeros(n, dtype=torch.float32, device="cuda")
+        sal.check_tiles(ctx, V, tiles[:n], Sr.clone(), tiles[:n], td, st, 0.02, err, exact_out=X)
+        for k, lo in enumerate(tiles[:n]):
+            assert torch.equal(X[k], ctx.raw_box(V, lo, td)), (n, lo)
