@@ -1014,8 +1014,15 @@ sal_status sal_check_tiles(sal_ctx *c, const float *V, int64_t n0, int64_t n1, i
     // face is part of the tile on the other side, whose own box computes the same energies: it
     // is copied from there (HALO_TABLE ints per copy) instead of computed again.  An energy does
     // not depend on the box that computes it, so the maps keep their bits.
+    // Finding the neighbours takes the host 0.1 us a tile and the copies a launch, which cheap
+    // energies do not repay: cubes below 6 share from L^3 times the tile's voxels = 90,000 on (1,000
+    // touching tiles at cube 5 of 8^3 309 us without, 385 with; of 9^3 311 and 314, of 12^3 199 and 138;
+    // at cube 3 of 8^3 263 and 379, of 16^3 115 and 117, of 20^3 153 and 134; at cube 6 of 4^3 337 and
+    // 341, of 6^3 447 and 379).
+    const int64_t tile_vox = tile_dims[0] * tile_dims[1] * tile_dims[2];
+    const bool share = c->L >= 6 || tile_vox * c->L * c->L * c->L >= 90000;
     TileIndex index{{}, n1, n2};
-    if (vol_stride == 0 && nbox > 1 && c->p.stride == 1) {
+    if (share && vol_stride == 0 && nbox > 1 && c->p.stride == 1) {
         index.at.reserve((size_t)nbox);
         for (int64_t b = 0; b < nbox; ++b) index.at.emplace_back(index.key(box_lo + 3 * b), (int)b);
         std::sort(index.at.begin(), index.at.end());

@@ -246,3 +246,20 @@ def test_padded_workgroups_of_a_batch(L, kw, td):
         sal.check_tiles(ctx, V, tiles[:n], Sr.clone(), tiles[:n], td, st, 0.02, err, exact_out=X)
         for k, lo in enumerate(tiles[:n]):
             assert torch.equal(X[k], ctx.raw_box(V, lo, td)), (n, lo)
+
+
+@pytest.mark.parametrize("L,td", [(5, (8, 9, 10)), (5, (8, 9, 9)), (4, (11, 11, 11)), (4, (11, 12, 12)), (3, (15, 15, 15)),
+                                  (3, (14, 15, 15)), (2, (22, 23, 23)), (2, (22, 22, 23)), (6, (2, 3, 4))])
+def test_touching_tiles_of_small_cubes(L, td):
+    """Either side of the size from which touching tiles take energies from each other (cubes below 6)."""
+    shape = tuple(2 * d + 5 for d in td)
+    V = torch.from_numpy(synth.make_volume(shape, seed=L, n_faults=1, throw=2)).cuda()
+    ctx = sal.Saliency(L=L)
+    _, _, Sr, st = ctx.saliency_maps(V)
+    tiles = [(a * td[0], b * td[1], c * td[2]) for a in range(2) for b in range(2) for c in range(2)]
+    X = torch.empty((len(tiles), 3) + td, dtype=torch.float32, device="cuda")
+    err = torch.zeros(len(tiles), dtype=torch.float32, device="cuda")
+    sal.check_tiles(ctx, V, tiles, Sr.clone(), tiles, td, st, 0.02, err, exact_out=X)
+    for k, lo in enumerate(tiles):
+        sl = (slice(None),) + tuple(slice(a, a + d) for a, d in zip(lo, td))
+        assert torch.equal(X[k], Sr[sl]), lo
