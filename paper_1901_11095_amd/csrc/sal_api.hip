@@ -796,26 +796,13 @@ static void lattice_box(const sal_ctx *c, const int64_t n[3], const int64_t eo[3
     }
 }
 
-// An upper bound of the energy kernels' workgroups for a box of k window positions per axis
-// that grows with the box: every fused tile holds at least 8 x 16 positions and walks at
-// least 2 of them along t; a sliding one holds one x position and 16 y positions for every
-// t segment its k[0] stride rows touch; the window-by-window kernel launches at most 4096.
-static int64_t energy_blocks_bound(const sal_ctx *c, const int64_t k[3])
-{
-    const int64_t slide = ((k[0] * c->p.stride + SLIDE_SEG - 1) / SLIDE_SEG + 2) * k[1] * ((k[2] + 15) / 16);
-    const int64_t other = uses_window_kernel(c) ? 4096 : ((k[1] + 7) / 8) * ((k[2] + 15) / 16) * ((k[0] + 1) / 2);
-    return other > slide ? other : slide;
-}
-
 // workspace of sal_raw_box: E of the grown box, then (stride > 1) the lattice energies it
-// interpolates, then the energy kernel's partials; kd bounds the lattice box
+// interpolates; kd bounds the lattice box.  (A box takes no partials.)
 static size_t raw_box_ws(const sal_ctx *c, const int64_t ed[3], const int64_t kd[3])
 {
-    const int64_t S = c->p.stride;
     size_t w = align256((size_t)3 * ed[0] * ed[1] * ed[2] * sizeof(float));
-    if (S > 1) w += align256((size_t)3 * kd[0] * kd[1] * kd[2] * sizeof(float));
-    const int64_t nb = energy_blocks_bound(c, S > 1 ? kd : ed);
-    return w + align256((size_t)nb * sizeof(float));
+    if (c->p.stride > 1) w += align256((size_t)3 * kd[0] * kd[1] * kd[2] * sizeof(float));
+    return w;
 }
 
 sal_status sal_raw_box_workspace_size(sal_ctx *c, const int64_t box_dims[3], size_t *bytes)
@@ -853,13 +840,11 @@ sal_status sal_raw_box(sal_ctx *c, const float *V, int64_t n0, int64_t n1, int64
     if ((st = sticky(c)) != SAL_OK) return st;
     char *ws = (char *)workspace;
     float *Eb = (float *)ws;
-    size_t off = align256((size_t)3 * ed[0] * ed[1] * ed[2] * sizeof(float));
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (c->p.stride > 1) {
         // the lattice energies around the grown box, interpolated onto it
-        float *El = (float *)(ws + off);
-        off += align256((size_t)3 * kd[0] * kd[1] * kd[2] * sizeof(float));
+        float *El = (float *)(ws + align256((size_t)3 * ed[0] * ed[1] * ed[2] * sizeof(float)));
         e = launch_energy(c, V, n0, n1, n2, vbox, El, nullptr, nullptr, s);
         if (e != hipSuccess) return dev_fail(c, e, "energy launch");
         e = launch_upsample_box(El, kd, klo, K, c->p.stride, eo, ed, Eb, s);

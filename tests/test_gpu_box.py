@@ -123,3 +123,32 @@ def test_raw_box_forms_of_the_comparison(rays, d, dims):
     for lo in ((0, 0, 0), tuple(n - k for n, k in zip(shape, dims)), tuple((n - k) // 2 for n, k in zip(shape, dims))):
         box = ctx.raw_box(V, lo, dims)
         assert torch.equal(box, Sr[:, lo[0]:lo[0] + dims[0], lo[1]:lo[1] + dims[1], lo[2]:lo[2] + dims[2]]), lo
+
+
+@pytest.mark.parametrize("L,kw", [(5, {}), (8, {}), (16, {}), (12, {}), (16, {"precision": sal.BF16_SPLIT}),
+                                  (16, {"stride": 4}), (8, {"stride": 3}), (12, {"stride": 3}), (9, {"stride": 9})])
+@pytest.mark.parametrize("dims", [(1, 100, 16), (17, 3, 21)])
+def test_raw_box_workspace_is_what_it_writes(L, kw, dims):
+    """The workspace holds the energies of the grown box and, at a stride, the lattice energies, and
+    nothing else: a buffer of exactly that size serves every place of the box, and no byte past it
+    changes."""
+    shape = (40, 120, 50)
+    V = torch.from_numpy(synth.make_volume(shape, seed=7, n_faults=1, throw=3)).cuda()
+    ctx = sal.Saliency(L=L, **kw)
+    _, _, Sr, _ = ctx.saliency_maps(V)
+    r, S = ctx.params.d // 2, ctx.params.stride
+    grown = [d + 2 * r for d in dims]
+
+    def up(n):
+        return (n + 255) // 256 * 256
+
+    need = up(12 * grown[0] * grown[1] * grown[2])
+    if S > 1:
+        k = [(g - 1) // S + 3 for g in grown]
+        need += up(12 * k[0] * k[1] * k[2])
+    assert ctx.raw_box_workspace_size(dims) == need
+    for lo in ((0, 0, 0), tuple((n - d) // 2 for n, d in zip(shape, dims)), tuple(n - d for n, d in zip(shape, dims))):
+        buf = torch.full((need + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+        box = ctx.raw_box(V, lo, dims, workspace=buf[:need])
+        assert torch.equal(box, Sr[:, lo[0]:lo[0] + dims[0], lo[1]:lo[1] + dims[1], lo[2]:lo[2] + dims[2]]), lo
+        assert bool(torch.all(buf[need:] == 0xA5)), lo
