@@ -127,3 +127,17 @@ def test_plain_streamed_rows_equal_whole_slabs(L, shape, slab, kw):
     _, Sr, _ = stream.plain_streamed(ctx, stream.pinned(V), slab=slab)
     torch.cuda.synchronize()
     assert torch.equal(Sr, ref)
+
+
+@pytest.mark.parametrize("shape,slab", [((7, 2, (1 << 20) + 3), 3), ((5, (1 << 20) + 1, 3), 2), ((5, 2, 1 << 20), 2)])
+def test_plain_streamed_sides_past_a_box(shape, slab):
+    """A volume longer than the largest box along an axis streams whole slabs, one of exactly that
+    length its slabs' own rows: both equal the resident volume bit for bit (cube 2 contracts every
+    window on its own)."""
+    V = np.random.default_rng(3).standard_normal(shape, dtype=np.float32)
+    ctx = sal.Saliency(L=2)
+    S, Sr, stats = stream.plain_streamed(ctx, stream.pinned(V), slab=slab)
+    ref, _, Sr_ref, st = ctx.saliency_maps(torch.from_numpy(V).cuda())
+    torch.cuda.synchronize()
+    assert torch.equal(Sr, Sr_ref)
+    assert torch.equal(stats[:7], st) and torch.equal(S, ref)
