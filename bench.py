@@ -68,8 +68,9 @@ def slide_kernel_flops_per_voxel(L: int = 16) -> int:
     """Flops per window as that kernel spends them: its update multiplies each plane bin by a
     few constants instead of each stored bin by a twiddle (rows v = 4q + r: 0, 15, 5, 15 flops at
     L = 16, 0, 5, 0, 5 at L = 8, and two adds per stored bin), and the bins kt and L - kt (beyond
-    the first eight ky also ky and -ky) share their weights, their magnitudes added first:
-    36,672 at L = 16, 4,848 at L = 8."""
+    the first eight ky also ky and -ky) share their weights, their magnitudes added first.  The
+    packed column, one of L/2, is counted as the others, though it spends some more: 36,672 at
+    L = 16, 4,848 at L = 8."""
     nb, h = L ** 3 // 2, L // 2 + 1
     products = (35 if L == 16 else 10) * L * L // 8
     sums = 4 * L * (h - 2 + 6 * h) + (L - 8) * L // 4 * (7 * h + L - 2)
@@ -720,6 +721,49 @@ def survey_L8_leg(args, dev):
     return out
 
 
+# The whole record is several times as long as the printed line; a reader that keeps the last 9 KB of
+# the output finds no JSON in a line cut at its head.
+LINE_LIMIT = 8000
+# left out of the line below the headline's own roofline: text, and figures that follow from others
+LINE_DROP = ("flops_convention", "flops_per_voxel", "flops_per_voxel_min", "counters", "training", "bound_scope", "sample",
+             "algorithmic_bytes", "hbm_gbps", "block", "oracle_blocks", "speedup_vs_plain_bf16_split",
+             "max_before_fallback", "mean_before_fallback", "tile", "kernel_ms", "kernels_ms", "peak", "unit", "workload",
+             "direct_equivalent_tflops", "kernel", "ms_per_step", "achieved", "plain_fp32_resident", "plain_bf16_split_resident")
+# whole parts that go, in this order, if the line is still too long
+LINE_SPARE = (("precision_table",), ("streamed",), ("forms", "strides"), ("legs",), ("forms",), ("cpu_baseline",), ("roofline",),
+              ("max_rel_err_vs_oracle",))
+
+
+def compact(record: dict) -> dict:
+    """The record as printed: the contract's keys and the headline's roofline as they are, the rest to
+    four digits without the parts of LINE_DROP, the error table as maxima per form [E, S_raw, S], and
+    no longer than LINE_LIMIT."""
+    def cut(v, drop=()):
+        if isinstance(v, dict):
+            return {k: cut(x, drop) for k, x in v.items() if k not in drop}
+        if isinstance(v, (list, tuple)):
+            return [cut(x, drop) for x in v]
+        return float("%.4g" % v) if isinstance(v, float) else v
+
+    out = dict(record)
+    for k in ("forms", "legs", "streamed", "max_rel_err_vs_oracle"):
+        out[k] = cut(record.get(k), LINE_DROP)
+    out["cpu_baseline"] = cut(record.get("cpu_baseline"))
+    out["roofline"] = cut(record.get("roofline"), ("flops_convention",))
+    if record.get("precision_table"):
+        out["precision_table"] = cut({
+            f: [max(r[m]["max"] for m in r if m.startswith("E_")), max(r[m]["max"] for m in r if m.startswith("S_")), r["S"]["max"]]
+            for f, r in record["precision_table"]["maps"].items()})
+    for path in LINE_SPARE:
+        if len(json.dumps(out)) <= LINE_LIMIT:
+            break
+        d = out
+        for k in path[:-1]:
+            d = d.get(k) or {}
+        d.pop(path[-1], None)
+    return out
+
+
 def main(argv=None):
     ap = argparse.ArgumentParser(description=__doc__.splitlines()[0])
     ap.add_argument("--gpus", type=int, default=1)
@@ -739,6 +783,7 @@ def main(argv=None):
     ap.add_argument("--slab", type=int, default=128, help="t-rows per streamed slab")
     ap.add_argument("--no-table", action="store_true",
                     help="skip the per-map error table of every form on the 64^3 volume")
+    ap.add_argument("--details", metavar="FILE", help="write the whole record, of which the printed line is an extract")
     ap.add_argument("--copy-calib", action="store_true",
                     help="only run a 1 GiB device copy (HBM counter calibration)")
     args = ap.parse_args(argv)
@@ -888,7 +933,10 @@ def main(argv=None):
         "precision_table": table,
         "cpu_baseline": cpu,
     }
-    print(json.dumps(line))
+    if args.details:
+        with open(args.details, "w") as fh:
+            json.dump(line, fh, indent=1)
+    print(json.dumps(compact(line)))
     return 0
 
 
