@@ -626,21 +626,26 @@ struct dcs_frame {
     int eo0, eo1, eo2, ed0, ed1, ed2, bo0, bo1, bo2, bd0, bd1, bd2;
 };
 // Index in a frame's axis (origin o, size d) of volume position u, reflected in [0, n); clamped
-// for the padding positions of edge tiles, whose results are never stored.
+// for the padding positions of edge tiles, whose results are never stored.  The frame of a whole
+// volume (!BOX) is the volume.
+template <bool BOX>
 __device__ __forceinline__ int frame_idx(int u, int n, int o, int d)
 {
+    if constexpr (!BOX) return refl_idx(u, n);
     const int i = refl_idx(u, n) - o;
     return i < 0 ? 0 : (i >= d ? d - 1 : i);
 }
 
-// R = r at compile time (unrolled neighbour loops), or 0 for any r.
-template <int R>
+// R = r at compile time (unrolled neighbour loops), or 0 for any r.  BOX: of a box, else of the whole
+// volume (fr unused).
+template <int R, bool BOX>
 __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, int n0, int n1,
                                                    int n2, dcs_frame fr, dcs_args a, int nbx, int nby, int tt,
                                                    float *__restrict__ S,
                                                    float *__restrict__ mm_part)
 {
     extern __shared__ float lds[];
+    if constexpr (!BOX) fr = dcs_frame{0, 0, 0, n0, n1, n2, 0, 0, 0, n0, n1, n2};
     const int64_t plane = (int64_t)fr.ed1 * fr.ed2, N = plane * fr.ed0;
     const int64_t NS = (int64_t)fr.bd0 * fr.bd1 * fr.bd2;
     const int bid = blockIdx.x;
@@ -677,13 +682,13 @@ __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, 
         for (int e = 0; e < DMAXE; ++e) {
             const int i = tid + 256 * e;
             const int ix = i / W[m], iy = i - ix * W[m];
-            gofs[m][e] = i < HW[m] ? frame_idx(fr.bo1 + x_base - hx[m] + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
-                                         frame_idx(fr.bo2 + y_base - hy[m] + iy, n2, fr.eo2, fr.ed2)
+            gofs[m][e] = i < HW[m] ? frame_idx<BOX>(fr.bo1 + x_base - hx[m] + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
+                                         frame_idx<BOX>(fr.bo2 + y_base - hy[m] + iy, n2, fr.eo2, fr.ed2)
                                    : -1;
         }
     float pv[3][DMAXE];
     auto fetch = [&](int m, int tl) {
-        const float *src = E + m * N + (int64_t)frame_idx(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane;
+        const float *src = E + m * N + (int64_t)frame_idx<BOX>(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane;
 #pragma unroll
         for (int e = 0; e < DMAXE; ++e) pv[m][e] = gofs[m][e] >= 0 ? src[gofs[m][e]] : 0.f;
     };
@@ -812,7 +817,7 @@ __global__ __launch_bounds__(256) void k_dcs_tiled(const float *__restrict__ E, 
 // and shifts them by one per step.  Maps x and y keep one plane each in LDS with its halo,
 // read at constant offsets.  The sums run in the order of k_dcs_tiled and dcs_box_at (the
 // + ray before the - ray, s = 1..r), so all three give the same bits.
-template <int R>
+template <int R, bool BOX>
 __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, int n0, int n1, int n2,
                                                   dcs_frame fr, dcs_args a, int nbx, int nby, int tt,
                                                   float *__restrict__ S,
@@ -826,6 +831,7 @@ __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, i
     __shared__ float pl2[HW2];
     __shared__ float red[4 * 6];
 
+    if constexpr (!BOX) fr = dcs_frame{0, 0, 0, n0, n1, n2, 0, 0, 0, n0, n1, n2};
     const int64_t plane = (int64_t)fr.ed1 * fr.ed2, N = plane * fr.ed0;
     const int64_t NS = (int64_t)fr.bd0 * fr.bd1 * fr.bd2;
     const int bid = blockIdx.x;
@@ -844,22 +850,22 @@ __global__ __launch_bounds__(256) void k_dcs_axis(const float *__restrict__ E, i
 #pragma unroll
     for (int e = 0; e < N1; ++e) {
         const int i = tid + 256 * e, ix = i / W1, iy = i % W1;
-        o1[e] = i < HW1 ? frame_idx(fr.bo1 + x_base - R + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
-                              frame_idx(fr.bo2 + y_base + iy, n2, fr.eo2, fr.ed2)
+        o1[e] = i < HW1 ? frame_idx<BOX>(fr.bo1 + x_base - R + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
+                              frame_idx<BOX>(fr.bo2 + y_base + iy, n2, fr.eo2, fr.ed2)
                         : -1;
     }
 #pragma unroll
     for (int e = 0; e < N2; ++e) {
         const int i = tid + 256 * e, ix = i / W2, iy = i % W2;
-        o2[e] = i < HW2 ? frame_idx(fr.bo1 + x_base + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
-                              frame_idx(fr.bo2 + y_base - R + iy, n2, fr.eo2, fr.ed2)
+        o2[e] = i < HW2 ? frame_idx<BOX>(fr.bo1 + x_base + ix, n1, fr.eo1, fr.ed1) * fr.ed2 +
+                              frame_idx<BOX>(fr.bo2 + y_base - R + iy, n2, fr.eo2, fr.ed2)
                         : -1;
     }
     const int o0 = valid ? (fr.bo1 + x - fr.eo1) * fr.ed2 + (fr.bo2 + y - fr.eo2) : 0;
     float col[D], nxt = 0.f, p1[N1], p2[N2];
-    auto at0 = [&](int tl) { return E[(int64_t)frame_idx(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane + o0]; };
+    auto at0 = [&](int tl) { return E[(int64_t)frame_idx<BOX>(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane + o0]; };
     auto fetch12 = [&](int tl) {
-        const float *src1 = E + N + (int64_t)frame_idx(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane, *src2 = src1 + N;
+        const float *src1 = E + N + (int64_t)frame_idx<BOX>(fr.bo0 + tl, n0, fr.eo0, fr.ed0) * plane, *src2 = src1 + N;
 #pragma unroll
         for (int e = 0; e < N1; ++e) p1[e] = o1[e] >= 0 ? src1[o1[e]] : 0.f;
 #pragma unroll
@@ -1290,7 +1296,9 @@ static dcs_args dcs_args_of(const sal_ctx *c)
     return a;
 }
 
-// The tiled comparison on a frame (its rays' planes fit the LDS).
+// The tiled comparison on a frame (its rays' planes fit the LDS); !BOX: of the whole volume, whose
+// frame is known to the compiler (128^3 at r = 2 24.6 us as a box, 22.4 so; at r = 8 31.9 and 29.9).
+template <bool BOX>
 static hipError_t launch_dcs_frame(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, int64_t n2,
                                    const dcs_frame &fr, float *S_raw, float *minmax_part, hipStream_t s)
 {
@@ -1305,8 +1313,8 @@ static hipError_t launch_dcs_frame(const sal_ctx *c, const float *E, int64_t n0,
                       a.rays[2] == (SAL_RAY_PY | SAL_RAY_MY);
 #define SAL_DCS_A(RR)                                                                                               \
     case RR:                                                                                                         \
-        hipLaunchKernelGGL(k_dcs_axis<RR>, dim3(nb), dim3(256), 0, s, E, (int)n0, (int)n1, (int)n2, fr, a, nbx, nby, tt, \
-                           S_raw, minmax_part);                                                                      \
+        hipLaunchKernelGGL((k_dcs_axis<RR, BOX>), dim3(nb), dim3(256), 0, s, E, (int)n0, (int)n1, (int)n2, fr, a, nbx, \
+                           nby, tt, S_raw, minmax_part);                                                             \
         return hipGetLastError();
     if (axis) {
         switch (c->r) {
@@ -1327,10 +1335,10 @@ static hipError_t launch_dcs_frame(const sal_ctx *c, const float *E, int64_t n0,
 #define SAL_DCS_T(RR)                                                                                               \
     do {                                                                                                             \
         if (lds > 65536)                                                                                             \
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_dcs_tiled<RR>),                              \
+            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_dcs_tiled<RR, BOX>),                         \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                         \
-        hipLaunchKernelGGL(k_dcs_tiled<RR>, dim3(nb), dim3(256), lds, s, E, (int)n0, (int)n1, (int)n2, fr, a, nbx, nby, \
-                           tt, S_raw, minmax_part);                                                                  \
+        hipLaunchKernelGGL((k_dcs_tiled<RR, BOX>), dim3(nb), dim3(256), lds, s, E, (int)n0, (int)n1, (int)n2, fr, a, \
+                           nbx, nby, tt, S_raw, minmax_part);                                                        \
     } while (0)
     // r known at compile time for the default d = L of every supported cube side
     switch (c->r) {
@@ -1355,7 +1363,7 @@ hipError_t launch_dcs(const sal_ctx *c, const float *E, int64_t n0, int64_t n1, 
 {
     const int d0 = (int)n0, d1 = (int)n1, d2 = (int)n2;
     if (dcs_tiled_lds_floats(c->p.rays, c->r) <= DCS_LDS_MAX_FLOATS)
-        return launch_dcs_frame(c, E, n0, n1, n2, dcs_frame{0, 0, 0, d0, d1, d2, 0, 0, 0, d0, d1, d2}, S_raw, minmax_part, s);
+        return launch_dcs_frame<false>(c, E, n0, n1, n2, dcs_frame{0, 0, 0, d0, d1, d2, 0, 0, 0, d0, d1, d2}, S_raw, minmax_part, s);
     hipLaunchKernelGGL(k_dcs, dim3((unsigned)dcs_num_blocks(c, n0, n1, n2)), dim3(256), 0, s, E, d0, d1, d2,
                        dcs_args_of(c), S_raw, minmax_part);
     return hipGetLastError();
@@ -1476,7 +1484,7 @@ hipError_t launch_dcs_box(const sal_ctx *c, const float *Eb, const int64_t eo[3]
         auto i = [](const int64_t *v, int k) { return (int)v[k]; };
         const dcs_frame fr{i(eo, 0), i(eo, 1), i(eo, 2), i(ed, 0), i(ed, 1), i(ed, 2),
                            i(bo, 0), i(bo, 1), i(bo, 2), i(bd, 0), i(bd, 1), i(bd, 2)};
-        return launch_dcs_frame(c, Eb, n[0], n[1], n[2], fr, S, nullptr, s);
+        return launch_dcs_frame<true>(c, Eb, n[0], n[1], n[2], fr, S, nullptr, s);
     }
     const dcs_args a = dcs_args_of(c);
     const int64_t nb = bd[0] * bd[1] * bd[2];
