@@ -25,6 +25,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -104,49 +105,73 @@ def gen_flops_per_voxel(L: int) -> int:
     return 4 * h * L + h * pair_dft_flops(L) + rows * per_row
 
 
-# What a committed counter record covers: the kernel template's own text, the device helpers
-# and the box geometry it reads (a launcher or host-side change leaves the record valid).
+# The source of the kernels a committed counter record is about.
 KERNEL_TEXT = {
-    "k_energy_slide": ("sal_energy_slide.hip", "k_energy_slide"),
-    "k_energy_f32": ("sal_kernels.hip", "k_energy_f32"),
-    "k_energy_h": ("sal_energy16.hip", "k_energy_h"),
-    "k_conv3": ("sal_net.hip", "k_conv3"),
+    "k_energy_slide": "sal_energy_slide.hip",
+    "k_energy_f32": "sal_kernels.hip",
+    "k_energy_h": "sal_energy16.hip",
+    "k_conv3": "sal_net.hip",
 }
 CSRC = os.path.join(ROOT, "paper_1901_11095_amd", "csrc")
 SURROGATE_FLOPS = 2 * 47952  # multiply-adds of the five convolutions per voxel
 
 
-def _function_text(path: str, name: str) -> str:
-    """The definition of the __global__ function `name` in `path`: from its declarator to the
-    brace that closes its body."""
-    with open(path) as fh:
-        src = fh.read()
-    i = src.find("void %s(" % name)
-    if i < 0:
-        raise KeyError(name)
-    j = src.index("{", i)
-    depth = 0
-    for k in range(j, len(src)):
-        if src[k] == "{":
-            depth += 1
-        elif src[k] == "}":
-            depth -= 1
-            if depth == 0:
-                return src[i:k + 1]
-    raise ValueError("unbalanced braces in %s" % path)
+def _read_source(name: str) -> str:
+    with open(os.path.join(CSRC, name)) as fh:
+        return fh.read()
 
 
-def kernel_source_hash(kernel: str) -> str:
-    h = hashlib.sha256()
-    fname, func = KERNEL_TEXT[kernel]
-    h.update(_function_text(os.path.join(CSRC, fname), func).encode())
-    with open(os.path.join(CSRC, "sal_device.h"), "rb") as fh:
-        h.update(fh.read())
-    with open(os.path.join(CSRC, "sal_internal.h")) as fh:
-        txt = fh.read()
-    a, b = txt.find("struct ebox {"), txt.find("// ------------------------------------------------------------------ launchers")
-    h.update(txt[a:b].encode())
-    return h.hexdigest()[:16]
+_DEFINITION = re.compile(r"^(?:template <[^\n]*>\n)?(?:struct (?P<struct>\w+)|(?:static )?constexpr (?P<const>[^;(]*);|"
+                         r"#define (?P<macro>\w+)[^\n]*|(?=[^\n]*__(?:device|global)__)(?P<head>[^;{]*)\{)", re.M)
+
+
+def _definitions(src: str) -> dict:
+    """Device functions, structs, constants and macros at the top level of a source without its
+    comments: name -> the texts of its definitions."""
+    src = re.sub(r"/\*.*?\*/|//[^\n]*", "", src, flags=re.S)
+    out = {}
+    for m in _DEFINITION.finditer(src):
+        names, end = [m.group("struct") or m.group("macro")], m.end()
+        if m.group("const"):
+            names = re.findall(r"(\w+) = ", m.group("const"))
+        elif not m.group("macro"):
+            depth, end = 0, src.index("{", m.start())
+            while True:
+                depth += {"{": 1, "}": -1}.get(src[end], 0)
+                end += 1
+                if depth == 0:
+                    break
+        if m.group("head"):  # the name is what stands before the last parenthesis group
+            head, depth, i = m.group("head").rstrip(), 0, 0
+            for i in range(len(head) - 1, -1, -1):
+                depth += {")": 1, "(": -1}.get(head[i], 0)
+                if depth == 0:
+                    break
+            names = [re.search(r"(\w+)\s*$", head[:i]).group(1)]
+        for name in names:
+            out.setdefault(name, []).append(" ".join(src[m.start():end].split()))
+    return out
+
+
+def kernel_definitions(kernel: str, read=_read_source) -> dict:
+    """What the kernel's code is made of: its own definition and, from its file and the shared
+    headers, those it uses, at any depth.  Comments, launchers and other kernels are not in it."""
+    defs = {}
+    for name in (KERNEL_TEXT[kernel], "sal_device.h", "sal_internal.h", "sal_dft.h"):
+        for k, v in _definitions(read(name)).items():
+            defs.setdefault(k, []).extend(v)
+    used, todo = {}, [kernel]
+    while todo:
+        k = todo.pop()
+        if k not in used:
+            used[k] = defs[k]
+            todo += [w for t in defs[k] for w in set(re.findall(r"\w+", t)) if w in defs]
+    return used
+
+
+def kernel_source_hash(kernel: str, read=_read_source) -> str:
+    used = kernel_definitions(kernel, read)
+    return hashlib.sha256(json.dumps(sorted(used.items())).encode()).hexdigest()[:16]
 
 
 def counters_from_profiles(kernel_tag: str, kernel: str):
@@ -735,9 +760,9 @@ LINE_SPARE = (("precision_table",), ("streamed",), ("forms", "strides"), ("legs"
 
 
 def compact(record: dict) -> dict:
-    """The record as printed: the contract's keys and the headline's roofline as they are, the rest to
-    four digits without the parts of LINE_DROP, the error table as maxima per form [E, S_raw, S], and
-    no longer than LINE_LIMIT."""
+    """The record as printed: the contract's keys as they are, the rest to four digits and without the
+    parts of LINE_DROP (the headline's roofline loses its text only), the error table as maxima per
+    form [E, S_raw, S], no longer than LINE_LIMIT."""
     def cut(v, drop=()):
         if isinstance(v, dict):
             return {k: cut(x, drop) for k, x in v.items() if k not in drop}

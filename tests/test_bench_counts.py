@@ -171,3 +171,32 @@ def test_printed_line_is_short():
         rec["legs"] = {"l%d" % i: dict(form, forms=rec["forms"]) for i in range(3)}
         out = bench.compact(rec)
         assert len(json.dumps(out)) <= bench.LINE_LIMIT and {k: out[k] for k in contract} == contract
+
+
+def test_counter_records_cover_the_kernel():
+    """A committed counter record counts as long as nothing the kernel is made of changes: helpers,
+    structs and constants in its file and the shared headers, not comments, launchers or others'."""
+    used = bench.kernel_definitions("k_energy_slide")
+    assert {"k_energy_slide", "products", "take", "quarter", "group_sums", "SlideGeo", "box_tile", "refl_idx", "mfma4"} <= set(used)
+    assert {"TileCfg", "Geo", "box_tile"} <= set(bench.kernel_definitions("k_energy_f32"))
+    assert {"gelu_f", "FPW", "conv_fu"} <= set(bench.kernel_definitions("k_conv3"))
+    assert not {"k_dcs_axis", "launch_slide_L", "batch_per_box", "launch_energy_slide"} & set(used)
+    before = bench.kernel_source_hash("k_energy_slide")
+
+    def edited(name, old, new):
+        def read(f):
+            src = bench._read_source(f)
+            if f == name:
+                assert old in src
+                src = src.replace(old, new)
+            return src
+        return bench.kernel_source_hash("k_energy_slide", read)
+
+    f = "sal_energy_slide.hip"
+    assert edited(f, "const float a = p.y * H;", "const float a = p.y * H + 0.f;") != before
+    assert edited("sal_device.h", "u = u < 0 ? -u : u;", "u = u < 0 ? 0 : u;") != before
+    assert edited(f, "constexpr int STY = 16", "constexpr int STY = 32") != before
+    assert edited(f, "// (x, y) as a complex number times (-i)^K", "// another comment") == before
+    assert edited(f, "while (np < 8 &&", "while (np < 4 &&") == before
+    assert edited("sal_device.h", "int opaque(int v)", "int opaque(int u)") == before
+
