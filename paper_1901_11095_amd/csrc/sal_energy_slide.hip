@@ -36,8 +36,10 @@
 // workgroups, the y positions and the magnitudes are those of the lattice windows only.  At cube
 // 16 stage 2 is then a larger part of the step and takes ky and -ky together: the cosine and sine
 // sums of both parts (16 rows for 16 ky, half the MFMAs) and eight additions.  Energies of stride 4
-// on 512^3 4.38 -> 3.74 ms; RMS error of E against FP64 at strides 2 to 7 0.96 to 1.02 times
-// what it was, 5.5e-8 to 9.6e-8.  S = 1 keeps one sum per row of P and its rounding.
+// on 512^3 4.38 -> 3.74 ms.  RMS error against FP64, of one sum per row of P: E 5.9e-8 to 8.8e-8, at
+// strides 2 to 7 over 12 small volumes each 0.997 to 1.005 times that, on 200 x 256 x 190 to 512^3
+// 0.995 to 0.997 times; S over 72 volumes 1.00 +- 0.02 times (of one volume 0.65 to 1.55: its scale
+// hangs on the errors of six extreme voxels).  S = 1 keeps one sum per row and its bits.
 // In wave 0 the bins (kt, ky) and (-kt, -ky) of the packed column sit in one lane; its
 // update is applied to U = Z[k] + conj Z[-k] = 2 D_{kx=0}[k] and V = Z[k] - conj Z[-k] =
 // 2i D_{kx=L/2}[k] instead (the plane spectra transformed the same way), so every slot is one
@@ -567,9 +569,11 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * (L / 2
 // touched by the box rows [o0, o0 + d0); the grid covers the most any box of the batch needs.
 static int slide_nseg(int o0, int d0, int r) { return slide_seg_id(o0 + d0 - 1, r) - slide_seg_id(o0, r) + 1; }
 
-// Parts a segment's windows are split into: one, more while the chip would not get two
-// workgroups per CU at cube 8 (one at cube 16: eight waves of 256 registers) and a part keeps
-// eight windows.  Each part repeats the earlier ones' updates, without magnitudes (a third of
+// Parts a segment's windows are split into: one, doubled up to eight while the chip would not get
+// two workgroups per CU at cube 8 (one at cube 16: eight waves of 256 registers) and the box has at
+// least eight rows of t for each part.  The rows are the box's: a segment that holds fewer (the first
+// has L/2 windows), or a stride S, leaves parts with fewer windows, down to none, which leave at once.
+// Each part repeats the earlier ones' updates, without magnitudes (a third of
 // a step's vector work, 0.7 of its time when one workgroup has a CU to itself), so splitting
 // only pays in latency, on idle CUs: 32^3 at cube 8 31.4 us in one part, 27.1 in two, 25.6 in
 // four; at cube 16 85 -> 73; 128 x 24 x 30 at cube 16 320 -> 244.  The sums are the same chain

@@ -1,15 +1,18 @@
-// Steps 1-3 of the saliency method (Shafiq et al., ICIP 2017, Sec. 2) window by window:
-// the local 3D DFT of each window (DFT definition after Eq. (2)), its plane projections
-// with DC excluded (Eqs. (1)-(4)) and the mean magnitudes E_t, E_x, E_y, with nothing
-// shared between windows.  Used where the fused kernels' sharing of the first two axes
-// between neighbouring windows does not apply or does not fit:
-//   * windows on a lattice of stride s >= 3 (Sec. 2 asks only for more than 50 % overlap,
-//     s < L/2) where the sliding kernel of cube 8 and 16 does not take them, and the
-//     non-overlapping s = L of the predecessor method (Sec. 1): the work falls by s^3 while
-//     unshared windows cost 2.5 times the shared contraction per window;
-//   * cube sides without a fused kernel (9..15, 17..20).
-// FP32; cube 16 on the matrix cores (k_energy_win_mfma below), the other sides on the vector
-// ALUs.  A workgroup walks windows (grid-stride over the windows of its box); per window:
+// Steps 1-3 of the saliency method (Shafiq et al., ICIP 2017, Sec. 2) where the fused kernels'
+// sharing of the first two axes between neighbouring windows does not apply or does not fit: the
+// local 3D DFT of each window (DFT definition after Eq. (2)), its plane projections with DC
+// excluded (Eqs. (1)-(4)) and the mean magnitudes E_t, E_x, E_y.
+//   * Cubes 9..15 and 17..20, windows at every voxel or on a lattice of overlapping stride (Sec. 2
+//     asks for more than 50 % overlap, s < L/2): runs of windows along y that share the first two
+//     stages (k_energy_run), unless the stage outputs of a run of eight leave no room for two
+//     workgroups on a CU (the widest strides of the largest cubes).
+//   * Everything else window by window, nothing shared (k_energy_win, at cube 16 k_energy_win_mfma):
+//     the non-overlapping stride s = L of the predecessor method (Sec. 1), overlapping strides of the
+//     other cubes that neither the sliding kernel of cube 8 and 16 nor the vector-ALU kernel of
+//     cubes 2..7 takes, and what does not fit a run.  The work falls by s^3 while unshared windows cost
+//     2.5 times the shared contraction per window.
+// FP32.  Window by window (cube 16 on the matrix cores, the other sides on the vector ALUs) a
+// workgroup walks windows, grid-stride over the windows of its box; per window:
 //   load    the L^3 samples, reflected at the volume faces, into LDS;
 //   stage A per column (q, r): A[mu][q][r] = sum_p W[mu, p] win[p][q][r], mu <= L/2;
 //   stage B per (mu, r): B[mu][nu][r] = sum_q W[nu, q] A[mu][q][r], every nu;

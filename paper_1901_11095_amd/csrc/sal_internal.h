@@ -233,12 +233,12 @@ hipError_t launch_tile_merge_boxes(float *S_raw, int64_t n0, int64_t n1, int64_t
                                    double bound, float *err, hipStream_t s);
 
 int64_t energy_gen_num_blocks(int L, int64_t d0, int64_t d1, int64_t d2, int64_t nbox = 1);
-// Window-by-window energies (strides >= 3, the non-overlapping stride L, cube sides without a
-// fused kernel): bx as for the fused kernels, windows at o + stride k.
+// Energies by runs of windows or window by window (strides >= 3, the non-overlapping stride L, cube
+// sides without a fused kernel): bx as for the fused kernels, windows at o + stride k.
 hipError_t launch_energy_win(const sal_ctx *c, const float *V, int64_t n0, int64_t n1, int64_t n2, const ebox &bx,
                              float *E, float *vmax_part, int *nparts, hipStream_t s, int nbox = 1);
 int64_t energy_win_num_blocks(const sal_ctx *c, int64_t k0, int64_t k1, int64_t k2);
-// Whether the energies of this context come from the window-by-window kernel.
+// Whether the energies of this context come from those kernels.
 inline bool uses_window_kernel(const sal_ctx *c)
 {
     const int L = c->L, S = c->p.stride;

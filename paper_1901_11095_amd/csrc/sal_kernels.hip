@@ -974,7 +974,7 @@ static int64_t dcs_tiled_lds_floats(const uint32_t rays[3], int r)
 static const int64_t DCS_LDS_MAX_FLOATS = 144 * 1024 / 4;
 
 // ------------------------------------------------------------------------------------
-// FP64 volume-wide statistics {lo_t, hi_t, lo_x, hi_x, lo_y, hi_y, max|V|} from partials.  One
+// Volume-wide statistics {lo_t, hi_t, lo_x, hi_x, lo_y, hi_y, max|V|} from partials, as FP64.  One
 // workgroup (the partials are some hundred KB at most); bound by the latency of its loads, so
 // 16 waves with four independent loads in flight each (cube 8 on 256 x 512 x 512, 32,768 + 6 x
 // 8,192 partials: 67 us with four waves and one load, 11 us).  The extremes of floats are floats:
@@ -1162,8 +1162,8 @@ __global__ __launch_bounds__(64) void k_project(const float2 *__restrict__ F, in
 // start (the operand tables and the first samples, some 2 us of the 56 a step takes at cube
 // 16 in split BF16), while its length is the grain of the last round of workgroups, 512 or 768
 // at a time: 32 steps where they leave at least 16 rounds, shorter down to two (the partials of
-// a volume are sized for two steps a workgroup; 128 x 256 x 256 in split BF16 7.82 -> 7.48 ms
-// for the pass).  A batch takes no partials, and fewer than half of its workgroups have work (its
+// a volume are sized for two steps a workgroup).  What it saves a volume is small (128 x 256 x 256 in
+// split BF16 7.63 -> 7.52 ms for the pass with all else that changed); it pays in batches.  A batch takes no partials, and fewer than half of its workgroups have work (its
 // entries are tiles and slabs a sixth of them): twice as many, down to one step (tile checks of
 // 10, 26, 51 and 11 tiles of 32^3 7.4 ms with 8,192, 7.0 ms with 16,384).
 static int tt_len_for(int64_t n0, int64_t tiles_xy, bool batch)
