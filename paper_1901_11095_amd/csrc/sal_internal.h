@@ -163,12 +163,14 @@ inline ebox framed_box(int o0, int o1, int o2, int d0, int d1, int d2, int S)
 // One box: a contiguous range of tiles per XCD, for its L2.  A batch: in dispatch order, every
 // entry spread over all XCDs; its entries differ in size by six and more (tiles and the slabs
 // beyond their faces), and ranges of them left XCDs idle while others worked (26 tiles of 32^3
-// at cube 16 in split BF16: 1,770 us in ranges, 1,418 us so).
+// at cube 16 in split BF16: 1,770 us in ranges, 1,418 us so).  RANGES keeps ranges in a batch, too,
+// for kernels whose neighbouring workgroups share their samples, little else, and differ little.
+template <bool RANGES = false>
 __device__ __forceinline__ int box_tile(ebox &bx, int *v)
 {
     *v = 0;
     if (!bx.table) return sal_dev::xcd_tile(blockIdx.x, gridDim.x);
-    const int t = blockIdx.x;
+    const int t = RANGES ? sal_dev::xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
     const int e = t / bx.per_box;
     const int *q = bx.table + ENERGY_TABLE * e;
     bx.o0 = q[0];

@@ -263,3 +263,20 @@ def test_touching_tiles_of_small_cubes(L, td):
     for k, lo in enumerate(tiles):
         sl = (slice(None),) + tuple(slice(a, a + d) for a, d in zip(lo, td))
         assert torch.equal(X[k], Sr[sl]), lo
+
+
+@pytest.mark.parametrize("L,stride", [(5, 5), (7, 3), (9, 9), (16, 16), (18, 8), (20, 8), (20, 9)])
+def test_window_by_window_batches(L, stride):
+    """Batches whose energies are taken window by window, in ranges of windows per XCD: one, two and
+    many tiles against the box of the same voxels, bit for bit."""
+    V = torch.from_numpy(synth.make_volume((61, 58, 77), seed=L, n_faults=1, throw=3)).cuda()
+    ctx = sal.Saliency(L=L, stride=stride)
+    _, _, Sr, st = ctx.saliency_maps(V)
+    td = (9, 14, 11)
+    tiles = [(a, b, c) for a in (0, 17, 52) for b in (0, 30, 44) for c in (1, 40, 66)]
+    for n in (1, 2, len(tiles)):
+        X = torch.empty((n, 3) + td, dtype=torch.float32, device="cuda")
+        err = torch.zeros(n, dtype=torch.float32, device="cuda")
+        sal.check_tiles(ctx, V, tiles[:n], Sr.clone(), tiles[:n], td, st, 0.02, err, exact_out=X)
+        for k, lo in enumerate(tiles[:n]):
+            assert torch.equal(X[k], ctx.raw_box(V, lo, td)), (n, lo)
