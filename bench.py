@@ -751,7 +751,7 @@ def survey_L8_leg(args, dev):
 LINE_LIMIT = 8000
 # left out of the line below the headline's own roofline: text, and figures that follow from others
 LINE_DROP = ("flops_convention", "flops_per_voxel", "flops_per_voxel_min", "counters", "training", "bound_scope", "sample",
-             "algorithmic_bytes", "hbm_gbps", "block", "oracle_blocks", "speedup_vs_plain_bf16_split",
+             "algorithmic_bytes", "hbm_gbps", "hbm_frac", "block", "oracle_blocks", "speedup_vs_plain_bf16_split",
              "max_before_fallback", "mean_before_fallback", "tile", "kernel_ms", "kernels_ms", "peak", "unit", "workload",
              "direct_equivalent_tflops", "kernel", "ms_per_step", "achieved", "plain_fp32_resident", "plain_bf16_split_resident")
 # whole parts that go, in this order, if the line is still too long
